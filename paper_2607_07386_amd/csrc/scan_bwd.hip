@@ -944,8 +944,7 @@ hipError_t sdm_launch_bwd_prep_range(const ScanBwdArgs& a, hipStream_t st) {
     const bool line = use_line(a, plan, &ok);
     if (!ok) return hipErrorInvalidConfiguration;
     SdmProfScope ps(SDM_K_BWD_PREP, st);
-    if (line) return line_pd(a) == BPD_LINE ? sdm_launch_bwd_prep<BPD_LINE>(a, st) : sdm_launch_bwd_prep<BPD>(a, st);
-    return plan.PD == 2 ? sdm_launch_bwd_prep<2>(a, st) : sdm_launch_bwd_prep<BPD>(a, st);
+    return sdm_launch_bwd_prep(a, line ? line_pd(a) : plan.PD, st);
 }
 
 hipError_t sdm_launch_bwd_scan_range(const ScanBwdArgs& a, hipStream_t st) {
