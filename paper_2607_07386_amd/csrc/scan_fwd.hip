@@ -764,11 +764,7 @@ bool sdm_fwd_plan_ok(int W, int R, int dv, int in_dtype) {
 
 hipError_t sdm_launch_fwd_prep_range(const ScanFwdArgs& a, hipStream_t st) {
     SdmProfScope ps(SDM_K_FWD_PREP, st);
-    switch (sdm_fwd_pd(a)) {
-        case 16: return sdm_launch_fwd_prep<16>(a, st);
-        case 8: return sdm_launch_fwd_prep<8>(a, st);
-        default: return sdm_launch_fwd_prep<FWD_PD>(a, st);
-    }
+    return sdm_launch_fwd_prep(a, 0, sdm_fwd_pd(a) - 1, st);
 }
 
 hipError_t sdm_launch_fwd_scan_range(const ScanFwdArgs& a, hipStream_t st) {

@@ -124,8 +124,10 @@ bool sdm_line_io_enabled();
 bool sdm_fwd_plan_ok(int W, int R, int dv, int in_dtype);
 size_t sdm_fwd_ws_bytes(int B, int H, int T, int W, int R);
 
-template <int PD>
-hipError_t sdm_launch_fwd_prep(const ScanFwdArgs& a, hipStream_t st);
+// Records of tokens [a.tb, a.te) for a scan that takes per = 1 << per_log2 tokens
+// a round (1: token by token) with `depth` rounds in flight: writers from token
+// (t / per - depth) per on are linked.
+hipError_t sdm_launch_fwd_prep(const ScanFwdArgs& a, int per_log2, int depth, hipStream_t st);
 
 // Chunk-parallel forward scan: tokens in chunks of SDM_CHUNK, W and R at most
 // SDM_CHUNK_MAX_LIST.  The coefficient kernel writes one record per (stream,
@@ -175,8 +177,7 @@ hipError_t sdm_launch_bwd_scan_range(const ScanBwdArgs& a, hipStream_t st);
 hipError_t sdm_launch_bwd_reduce_range(const ScanBwdArgs& a, hipStream_t st);
 // whether the backward of this shape runs the line-cooperative kernel now
 bool sdm_bwd_line_io(const ScanBwdArgs& a);
-template <int PD>
-hipError_t sdm_launch_bwd_prep(const ScanBwdArgs& a, hipStream_t st);
+hipError_t sdm_launch_bwd_prep(const ScanBwdArgs& a, int pd, hipStream_t st);
 bool sdm_bwd_plan_ok(int W, int R, int dv, int in_dtype);
 size_t sdm_bwd_ws_bytes(int B, int H, int T, int W, int R, int dv);
 
