@@ -764,15 +764,19 @@ bool sdm_fwd_plan_ok(int W, int R, int dv, int in_dtype) {
 
 hipError_t sdm_launch_fwd_prep_range(const ScanFwdArgs& a, hipStream_t st) {
     SdmProfScope ps(SDM_K_FWD_PREP, st);
+    int per_log2, depth, lds;
+    if (sdm_round_scan(a, &per_log2, &depth, &lds)) return sdm_launch_fwd_prep(a, per_log2, depth, st);
     return sdm_launch_fwd_prep(a, 0, sdm_fwd_pd(a) - 1, st);
 }
 
 hipError_t sdm_launch_fwd_scan_range(const ScanFwdArgs& a, hipStream_t st) {
+    SdmProfScope ps(SDM_K_FWD_SCAN, st);
+    int per_log2, depth, lds;
+    if (sdm_round_scan(a, &per_log2, &depth, &lds)) return sdm_launch_round_scan(a, st);
     FwdPlan p;
     if (!fwd_plan(a.B * a.H, a.W, a.R, a.dv, a.in_dtype, &p)) return hipErrorInvalidConfiguration;
     const bool save = a.saved != nullptr;
     const int pd = sdm_fwd_pd(a);
-    SdmProfScope ps(SDM_K_FWD_SCAN, st);
     if (a.in_dtype == SDM_DT_BF16)
         return save ? launch_fwd_kk<bf16_t, true>(a, p, pd, st) : launch_fwd_kk<bf16_t, false>(a, p, pd, st);
     return save ? launch_fwd_kk<float, true>(a, p, pd, st) : launch_fwd_kk<float, false>(a, p, pd, st);
@@ -795,6 +799,8 @@ size_t fwd_lds_k(const ScanFwdArgs& a, const FwdPlan& p, int pd, bool save) {
 // LDS of one workgroup of the forward scan these arguments launch (the kernel
 // and depth sdm_launch_fwd_scan_range picks).
 size_t sdm_fwd_scan_lds(const ScanFwdArgs& a) {
+    int per_log2, depth, lds;
+    if (sdm_round_scan(a, &per_log2, &depth, &lds)) return (size_t)lds;
     FwdPlan p;
     if (!fwd_plan(a.B * a.H, a.W, a.R, a.dv, a.in_dtype, &p)) return 0;
     const int pd = sdm_fwd_pd(a);

@@ -109,6 +109,10 @@ size_t sdm_fwd_scan_lds(const ScanFwdArgs& a);   // LDS of one workgroup of that
 // the two halves separately (records of [tb, te), then the scan of [tb, te))
 hipError_t sdm_launch_fwd_prep_range(const ScanFwdArgs& a, hipStream_t st);
 hipError_t sdm_launch_fwd_scan_range(const ScanFwdArgs& a, hipStream_t st);
+// The scan in rounds of tokens (scan_round.hip): whether these arguments take it,
+// with the prep kernel's window and a workgroup's LDS; and its launch.
+bool sdm_round_scan(const ScanFwdArgs& a, int* per_log2, int* depth, int* lds);
+hipError_t sdm_launch_round_scan(const ScanFwdArgs& a, hipStream_t st);
 // SIMDs (4 per compute unit) of the current device; 1024 if it cannot be queried.
 int sdm_device_simds();
 // Forced scan slice width (8 or 16), or 0 for the automatic choice.

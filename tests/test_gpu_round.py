@@ -1,0 +1,82 @@
+"""The forward scan in rounds of tokens against the oracle: list lengths at the
+edges of its rows-per-lane steps, row widths that leave lanes of the last column
+group without columns, sequences that end inside a round, tables small enough
+that most tokens share slots (waits inside a round, ring rows of earlier
+rounds) and large enough that few do, with and without the undo log; and with
+helper workgroups, which must not change a bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2607_07386_amd import sdm
+from tests.gpu_util import DEV, REGRESSION_TOL, rel_err
+
+pytestmark = pytest.mark.gpu
+
+# (streams, T, N, W, R, d_v)
+SHAPES = {
+    "one-row": (3, 37, 5, 1, 1, 32),
+    "k1-full": (2, 200, 40, 8, 8, 64),
+    "k1-odd": (3, 41, 30, 7, 3, 36),
+    "k2": (2, 65, 64, 16, 16, 32),
+    "k2-odd": (2, 50, 64, 9, 15, 100),
+    "k4-dense": (2, 150, 40, 32, 32, 64),
+    "k4-sparse": (16, 160, 4096, 32, 32, 32),
+    "k4-mixed": (3, 77, 200, 32, 17, 128),
+    "k8-dense": (2, 130, 80, 64, 64, 32),
+    "k8-sparse": (8, 131, 9000, 64, 64, 64),
+    "k8-mixed": (3, 53, 300, 48, 24, 100),
+    "k8-edge": (2, 4, 99, 33, 64, 44),
+}
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_round_scan(name, dtype):
+    S, T, N, W, R, dv = SHAPES[name]
+    rng = np.random.default_rng(1000 + len(name) * 7 + W + R)
+    lists = lambda k: np.stack([np.stack([np.sort(rng.choice(N, k, replace=False)) for _ in range(T)])
+                                for _ in range(S)]).astype(np.int32)
+    wi, ri = lists(W), lists(R)
+    wv = (rng.random((S, T, W)) * 2 / np.sqrt(W)).astype(np.float32)
+    rv = rng.random((S, T, R)).astype(np.float32)
+    dev = lambda a, dt=None: torch.from_numpy(np.ascontiguousarray(a))[:, None].to(DEV, dt)
+    v, al, be = (dev(x.astype(np.float32), dtype) for x in (rng.standard_normal((S, T, dv)), rng.uniform(0.1, 1, (S, T)),
+                                                            rng.uniform(0.1, 1, (S, T))))
+    m0 = rng.standard_normal((S, N, dv)).astype(np.float32)
+    f64 = lambda t: t[:, 0].double().cpu().numpy()
+    memo = m0.astype(np.float64)
+    yo, so = oracle.scan_fwd(wi, wv, ri, rv, f64(v), f64(al), f64(be), memo, save=True)
+
+    def run(save):
+        mem, saved = dev(m0), sdm.saved_buffer(S, 1, T, W, dv, DEV) if save else None
+        y = sdm.scan_fwd(dev(wi), dev(wv), dev(ri), dev(rv), v, al, be, mem, saved=saved)
+        torch.cuda.synchronize()
+        return y, mem, saved
+
+    y, mem, saved = run(True)
+    # fp32 sums of up to 64 terms on both sides of the recurrence
+    for got, ref in ((y, yo), (mem, memo), (saved, so)):
+        assert rel_err(f64(got), np.asarray(ref).reshape(f64(got).shape)) <= REGRESSION_TOL
+    y2, mem2, _ = run(False)
+    assert torch.equal(y, y2) and torch.equal(mem, mem2)
+
+
+def test_round_scan_stages_and_helpers():
+    """Stages of 64 tokens (no helpers) and one stage of 700 (helpers) of the same
+    call: the same bits, also against a table row's value carried over a stage."""
+    B, H, T, s, k, d = 1, 4, 700, 64, 32, 64
+    g = torch.Generator(device=DEV).manual_seed(5)
+    n = lambda *sh: torch.randn(sh, generator=g, device=DEV)
+    q, kk, v = (n(B, H, T, d).bfloat16() for _ in range(3))
+    al, be = (torch.sigmoid(n(B, H, T)).bfloat16() for _ in range(2))
+    cb = n(H, 2, s, d // 2).bfloat16()
+    out = []
+    for chunk in (0, 64, 192):
+        mem = torch.zeros((B, H, s * s, d), device=DEV)
+        o = sdm.forward(q, kk, cb, cb, v, al, be, mem, s * s, k, chunk=chunk)
+        torch.cuda.synchronize()
+        out.append((o["y"], mem))
+    for y, mem in out[1:]:
+        assert torch.equal(y, out[0][0]) and torch.equal(mem, out[0][1])
