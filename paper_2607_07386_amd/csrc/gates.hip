@@ -21,7 +21,9 @@ __device__ __forceinline__ float ld1(const VT* p, size_t i) {
 }
 
 // ---------------------------------------------------------------- gates
-template <typename VT>
+// Index type IT: 32 bits where the element count allows (a 64-bit division is
+// a hundred instructions and more).
+template <typename VT, typename IT>
 __global__ __launch_bounds__(256) void gates_kernel(const VT* __restrict__ a, const VT* __restrict__ b,
                                                     const float* __restrict__ A, const float* __restrict__ bdt,
                                                     int H, int T, int64_t n, float* __restrict__ alpha,
@@ -29,16 +31,19 @@ __global__ __launch_bounds__(256) void gates_kernel(const VT* __restrict__ a, co
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     float al = ld1(a, i), be = ld1(b, i);
-    sdm_gates_of(A, bdt, (int)((i / T) % H), al, be);
+    sdm_gates_of(A, bdt, (int)((IT)i / (IT)T % (IT)H), al, be);
     alpha[i] = al;
     beta[i] = be;
 }
 
 // One workgroup per head: every (b, t) of the head, in a fixed order per
-// thread, then a fixed tree over the threads.  dz = dalpha * (-A alpha
+// thread, then a fixed tree over the threads.  Bound by the few workgroups'
+// exponentials and logarithms: 16 waves a head, and no division (64 streams of
+// 4096 tokens, 16 heads, with the forward gates: 100 us by 4 waves dividing a
+// flat index by T per element, 47 now).  dz = dalpha * (-A alpha
 // sigma(z)), da = dz, db = dbeta beta (1 - beta); dA and db_dt are the head's
 // sums of dalpha * (-softplus(z) alpha) and of dz.
-constexpr int GB_THREADS = 256;
+constexpr int GB_THREADS = 1024;
 template <typename VT>
 __global__ __launch_bounds__(GB_THREADS) void gates_bwd_kernel(
     const VT* __restrict__ a, const VT* __restrict__ b, const float* __restrict__ A,
@@ -49,20 +54,21 @@ __global__ __launch_bounds__(GB_THREADS) void gates_bwd_kernel(
     const int h = blockIdx.x;
     const float Ah = A[h], bh = bdt[h];
     float sA = 0.f, sb = 0.f;
-    const int64_t per_head = (int64_t)B * T;
-    for (int64_t j = threadIdx.x; j < per_head; j += GB_THREADS) {
-        const int bb = (int)(j / T), t = (int)(j % T);
-        const size_t i = ((size_t)bb * H + h) * T + t;
-        const float z = ld1(a, i) + bh;
-        const float sp = sdm_softplus(z);
-        const float al = expf(-Ah * sp);
-        const float dal = dalpha[i];
-        const float dz = dal * (-Ah * al * sdm_sigmoid(z));
-        da[i] = dz;
-        sb += dz;
-        sA += dal * (-sp * al);
-        const float be = sdm_sigmoid(ld1(b, i));
-        db[i] = dbeta[i] * be * (1.f - be);
+    for (int bb = 0; bb < B; ++bb) {
+        const size_t base = ((size_t)bb * H + h) * T;
+        for (int t = threadIdx.x; t < T; t += GB_THREADS) {
+            const size_t i = base + t;
+            const float z = ld1(a, i) + bh;
+            const float sp = sdm_softplus(z);
+            const float al = expf(-Ah * sp);
+            const float dal = dalpha[i];
+            const float dz = dal * (-Ah * al * sdm_sigmoid(z));
+            da[i] = dz;
+            sb += dz;
+            sA += dal * (-sp * al);
+            const float be = sdm_sigmoid(ld1(b, i));
+            db[i] = dbeta[i] * be * (1.f - be);
+        }
     }
     red[0][threadIdx.x] = sA;
     red[1][threadIdx.x] = sb;
@@ -97,24 +103,36 @@ __device__ __forceinline__ float row_sum(float v) {
     return v;
 }
 
+// A row's pieces of this lane: quad q + j LPR of the row's d_v / 4, j < NQ (zeros
+// past the end).  Rows of up to 8 quads a lane are loaded once and kept in
+// registers; longer ones (NQ = 16) are read again where they are used.
+template <int LPR, int NQ, typename T>
+__device__ __forceinline__ void row_load(v4f (&x)[NQ], const T* p, int dv, int q) {
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+        const int c = q * 4 + j * 4 * LPR;
+        x[j] = c < dv ? ld4v(p + c) : v4zero();
+    }
+}
+
 // 1 / sqrt(mean(y^2) + eps) of one row; every lane of the row's group gets it
-template <int LPR>
-__device__ __forceinline__ float row_rstd(const float* yr, int dv, int q, float eps) {
+template <int LPR, int NQ>
+__device__ __forceinline__ float row_rstd(const v4f (&v)[NQ], int dv, float eps) {
     float ss = 0.f;
-    for (int c = q * 4; c < dv; c += 4 * LPR) {
-        const v4f v = ld4(yr + c);
-        ss = fmaf(v.x, v.x, ss);
-        ss = fmaf(v.y, v.y, ss);
-        ss = fmaf(v.z, v.z, ss);
-        ss = fmaf(v.w, v.w, ss);
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+        ss = fmaf(v[j].x, v[j].x, ss);
+        ss = fmaf(v[j].y, v[j].y, ss);
+        ss = fmaf(v[j].z, v[j].z, ss);
+        ss = fmaf(v[j].w, v[j].w, ss);
     }
     ss = row_sum<LPR>(ss);
     return 1.f / sqrtf(ss / (float)dv + eps);
 }
 
 // Rows are the tokens [tb, tb + tn) of every stream of T tokens: row r of
-// [0, S tn) is stream r / tn, token tb + r % tn.
-template <typename GT, int LPR>
+// [0, S tn) is stream r / tn, token tb + r % tn (IT: 32 bits where S tn allows).
+template <typename GT, int LPR, int NQ, typename IT>
 __global__ __launch_bounds__(256) void norm_gate_kernel(const float* __restrict__ y, const GT* __restrict__ g,
                                                         const float* __restrict__ gamma, float eps, int act,
                                                         int64_t rows, int T, int tb, int tn, int dv,
@@ -123,23 +141,26 @@ __global__ __launch_bounds__(256) void norm_gate_kernel(const float* __restrict_
     const int lane = threadIdx.x & 63, q = lane % LPR;
     const int64_t vrow = ((int64_t)blockIdx.x * 4 + threadIdx.x / 64) * RPW + lane / LPR;
     const bool ok = vrow < rows;
-    const int64_t vr = ok ? vrow : rows - 1;   // every lane takes part in the row sums
-    const int64_t row = (vr / tn) * T + tb + vr % tn;
-    const int64_t rr = row;
-    const float* yr = y + rr * dv;
-    const float rs = row_rstd<LPR>(yr, dv, q, eps);
+    const IT vr = (IT)(ok ? vrow : rows - 1);   // every lane takes part in the row sums
+    const int64_t row = (int64_t)(vr / (IT)tn) * T + tb + (int64_t)(vr % (IT)tn);
+    v4f v[NQ];
+    row_load<LPR, NQ>(v, y + row * dv, dv, q);
+    const float rs = row_rstd<LPR, NQ>(v, dv, eps);
     if (!ok) return;
     if (rstd && q == 0) rstd[row] = rs;
-    for (int c = q * 4; c < dv; c += 4 * LPR) {
-        const v4f v = ld4(yr + c);
-        const v4f gg = ld4v(g + rr * dv + c);
-        const v4f gm = gamma ? ld4(gamma + c) : v4f{1.f, 1.f, 1.f, 1.f};
-        v4f out;
-        out.x = v.x * rs * gm.x * act_f(gg.x, act);
-        out.y = v.y * rs * gm.y * act_f(gg.y, act);
-        out.z = v.z * rs * gm.z * act_f(gg.z, act);
-        out.w = v.w * rs * gm.w * act_f(gg.w, act);
-        st4(o + rr * dv + c, out);
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+        const int c = q * 4 + j * 4 * LPR;
+        if (c < dv) {
+            const v4f gg = ld4v(g + row * dv + c);
+            const v4f gm = gamma ? ld4(gamma + c) : v4f{1.f, 1.f, 1.f, 1.f};
+            v4f out;
+            out.x = v[j].x * rs * gm.x * act_f(gg.x, act);
+            out.y = v[j].y * rs * gm.y * act_f(gg.y, act);
+            out.z = v[j].z * rs * gm.z * act_f(gg.z, act);
+            out.w = v[j].w * rs * gm.w * act_f(gg.w, act);
+            st4(o + row * dv + c, out);
+        }
     }
 }
 
@@ -147,12 +168,14 @@ __global__ __launch_bounds__(256) void norm_gate_kernel(const float* __restrict_
 // dy = rstd (dn - n mean(dn n)).  dgamma: each workgroup sums do phi(g) n over
 // its rows in a fixed order (per lane across the rows its row group visits,
 // then over row groups and waves through LDS) into part[workgroup][d_v].
+// HBM-bound: y, g and do are read once (kept in registers up to NQ = 8).
 template <typename GT, int LPR, int NQ>
 __global__ __launch_bounds__(256) void norm_gate_bwd_kernel(
     const float* __restrict__ y, const GT* __restrict__ g, const float* __restrict__ gamma, float eps, int act,
     const float* __restrict__ dout, int64_t rows, int dv, int iters, float* __restrict__ dy,
     float* __restrict__ dg, float* __restrict__ part) {
     constexpr int RPW = 64 / LPR;
+    constexpr int NK = NQ <= 8 ? NQ : 1;   // quads of g and do kept
     extern __shared__ float gsum[];   // [4 * RPW][dv]
     const int lane = threadIdx.x & 63, q = lane % LPR, wave = threadIdx.x / 64;
     const int grp = wave * RPW + lane / LPR;     // row group of this lane in the workgroup
@@ -163,19 +186,33 @@ __global__ __launch_bounds__(256) void norm_gate_bwd_kernel(
         const int64_t row = ((int64_t)blockIdx.x * iters + it) * (4 * RPW) + grp;
         const bool ok = row < rows;
         const int64_t rr = ok ? row : rows - 1;
-        const float* yr = y + rr * dv;
-        const float rs = row_rstd<LPR>(yr, dv, q, eps);
+        v4f v[NQ], dk[NK], gk[NK];
+        row_load<LPR, NQ>(v, y + rr * dv, dv, q);
+        if constexpr (NK == NQ) {
+            row_load<LPR, NQ>(dk, dout + rr * dv, dv, q);
+            row_load<LPR, NQ>(gk, g + rr * dv, dv, q);
+        }
+        auto load = [&](int j, int c, v4f& d, v4f& gg) {
+            if constexpr (NK == NQ) {
+                d = dk[j];
+                gg = gk[j];
+            } else {
+                d = ld4(dout + rr * dv + c);
+                gg = ld4v(g + rr * dv + c);
+            }
+        };
+        const float rs = row_rstd<LPR, NQ>(v, dv, eps);
         // mean(dn n) over the row
         float dot = 0.f;
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
             const int c = q * 4 + j * 4 * LPR;
             if (c < dv) {
-                const v4f v = ld4(yr + c), d = ld4(dout + rr * dv + c);
-                const v4f gg = ld4v(g + rr * dv + c);
+                v4f d, gg;
+                load(j, c, d, gg);
                 const v4f gm = gamma ? ld4(gamma + c) : v4f{1.f, 1.f, 1.f, 1.f};
-                dot += d.x * act_f(gg.x, act) * gm.x * v.x + d.y * act_f(gg.y, act) * gm.y * v.y +
-                       d.z * act_f(gg.z, act) * gm.z * v.z + d.w * act_f(gg.w, act) * gm.w * v.w;
+                dot += d.x * act_f(gg.x, act) * gm.x * v[j].x + d.y * act_f(gg.y, act) * gm.y * v[j].y +
+                       d.z * act_f(gg.z, act) * gm.z * v[j].z + d.w * act_f(gg.w, act) * gm.w * v[j].w;
             }
         }
         dot = row_sum<LPR>(dot) * rs / (float)dv;   // mean(dn n) = rstd mean(dn y)
@@ -184,11 +221,11 @@ __global__ __launch_bounds__(256) void norm_gate_bwd_kernel(
         for (int j = 0; j < NQ; ++j) {
             const int c = q * 4 + j * 4 * LPR;
             if (c < dv) {
-                const v4f v = ld4(yr + c), d = ld4(dout + rr * dv + c);
-                const v4f gg = ld4v(g + rr * dv + c);
+                v4f d, gg;
+                load(j, c, d, gg);
                 const v4f gm = gamma ? ld4(gamma + c) : v4f{1.f, 1.f, 1.f, 1.f};
                 v4f n, ph, odg, ody;
-                n.x = v.x * rs; n.y = v.y * rs; n.z = v.z * rs; n.w = v.w * rs;
+                n.x = v[j].x * rs; n.y = v[j].y * rs; n.z = v[j].z * rs; n.w = v[j].w * rs;
                 ph.x = act_f(gg.x, act); ph.y = act_f(gg.y, act); ph.z = act_f(gg.z, act); ph.w = act_f(gg.w, act);
                 odg.x = d.x * gm.x * n.x * act_grad(gg.x, act);
                 odg.y = d.y * gm.y * n.y * act_grad(gg.y, act);
@@ -220,14 +257,29 @@ __global__ __launch_bounds__(256) void norm_gate_bwd_kernel(
     }
 }
 
-// out[c] = sum over blocks of part[block][c], blocks in order
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ part, int nblk, int dv,
-                                                     float* __restrict__ out) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= dv) return;
+// out[c] = sum over blocks of part[block][c]: 32 columns per workgroup, the
+// blocks over 32 threads (stride 32, in order), then a fixed tree.  One thread
+// per column walked all blocks (2048 dependent adds behind their loads): 470 us
+// of a 575 us epilogue backward of 262,144 rows of 128.
+constexpr int CS_COLS = 32, CS_PARTS = 32;
+__global__ __launch_bounds__(CS_COLS* CS_PARTS) void colsum_kernel(const float* __restrict__ part, int nblk, int dv,
+                                                                    float* __restrict__ out) {
+    __shared__ float red[CS_PARTS][CS_COLS];
+    const int x = threadIdx.x % CS_COLS, p = threadIdx.x / CS_COLS;
+    const int c = blockIdx.x * CS_COLS + x;
     float sum = 0.f;
-    for (int b = 0; b < nblk; ++b) sum += part[(size_t)b * dv + c];
-    out[c] = sum;
+    if (c < dv) {
+#pragma unroll 8
+        for (int b = p; b < nblk; b += CS_PARTS) sum += part[(size_t)b * dv + c];
+    }
+    red[p][x] = sum;
+    __syncthreads();
+#pragma unroll
+    for (int m = CS_PARTS / 2; m > 0; m >>= 1) {
+        if (p < m) red[p][x] += red[p + m][x];
+        __syncthreads();
+    }
+    if (p == 0 && c < dv) out[c] = red[0][x];
 }
 
 int lanes_per_row(int dv) {
@@ -235,15 +287,30 @@ int lanes_per_row(int dv) {
     return quads <= 8 ? 8 : quads <= 16 ? 16 : quads <= 32 ? 32 : 64;
 }
 
-template <typename GT, int LPR>
-hipError_t launch_norm_gate_l(const float* y, const void* g, const float* gamma, float eps, int act, int64_t S,
+template <typename GT, int LPR, int NQ>
+hipError_t launch_norm_gate_q(const float* y, const void* g, const float* gamma, float eps, int act, int64_t S,
                               int T, int tb, int tn, int dv, float* o, float* rstd, hipStream_t st) {
     constexpr int RPB = 4 * (64 / LPR);
     const int64_t rows = S * tn;
     const unsigned blocks = (unsigned)((rows + RPB - 1) / RPB);
-    hipLaunchKernelGGL((norm_gate_kernel<GT, LPR>), dim3(blocks), dim3(256), 0, st, y, static_cast<const GT*>(g),
-                       gamma, eps, act, rows, T, tb, tn, dv, o, rstd);
+    auto kfn = rows >> 31 ? norm_gate_kernel<GT, LPR, NQ, uint64_t> : norm_gate_kernel<GT, LPR, NQ, uint32_t>;
+    hipLaunchKernelGGL(kfn, dim3(blocks), dim3(256), 0, st, y, static_cast<const GT*>(g), gamma, eps, act, rows, T, tb,
+                       tn, dv, o, rstd);
     return hipGetLastError();
+}
+
+// quads per lane: 1 below 64 lanes a row
+template <typename GT, int LPR>
+hipError_t launch_norm_gate_l(const float* y, const void* g, const float* gamma, float eps, int act, int64_t S,
+                              int T, int tb, int tn, int dv, float* o, float* rstd, hipStream_t st) {
+    const int nq = (dv / 4 + LPR - 1) / LPR;
+    if constexpr (LPR == 64) {
+        if (nq > 8) return launch_norm_gate_q<GT, 64, 16>(y, g, gamma, eps, act, S, T, tb, tn, dv, o, rstd, st);
+        if (nq > 4) return launch_norm_gate_q<GT, 64, 8>(y, g, gamma, eps, act, S, T, tb, tn, dv, o, rstd, st);
+        if (nq > 2) return launch_norm_gate_q<GT, 64, 4>(y, g, gamma, eps, act, S, T, tb, tn, dv, o, rstd, st);
+        if (nq > 1) return launch_norm_gate_q<GT, 64, 2>(y, g, gamma, eps, act, S, T, tb, tn, dv, o, rstd, st);
+    }
+    return launch_norm_gate_q<GT, LPR, 1>(y, g, gamma, eps, act, S, T, tb, tn, dv, o, rstd, st);
 }
 
 template <typename GT>
@@ -291,12 +358,14 @@ hipError_t launch_ng_bwd_l(const float* y, const void* g, const float* gamma, fl
     int iters;
     int64_t nblk;
     ng_bwd_geometry<LPR>(rows, &iters, &nblk);
-    const int nq = (dv / 4 + LPR - 1) / LPR;
-    if (nq <= 1) return launch_ng_bwd_q<GT, LPR, 1>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st, iters, nblk);
-    if (nq <= 2) return launch_ng_bwd_q<GT, LPR, 2>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st, iters, nblk);
-    if (nq <= 4) return launch_ng_bwd_q<GT, LPR, 4>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st, iters, nblk);
-    if (nq <= 8) return launch_ng_bwd_q<GT, LPR, 8>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st, iters, nblk);
-    return launch_ng_bwd_q<GT, LPR, 16>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st, iters, nblk);
+    if constexpr (LPR == 64) {   // quads per lane: 1 below 64 lanes a row
+        const int nq = (dv / 4 + LPR - 1) / LPR;
+        if (nq > 8) return launch_ng_bwd_q<GT, 64, 16>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st, iters, nblk);
+        if (nq > 4) return launch_ng_bwd_q<GT, 64, 8>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st, iters, nblk);
+        if (nq > 2) return launch_ng_bwd_q<GT, 64, 4>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st, iters, nblk);
+        if (nq > 1) return launch_ng_bwd_q<GT, 64, 2>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st, iters, nblk);
+    }
+    return launch_ng_bwd_q<GT, LPR, 1>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st, iters, nblk);
 }
 
 template <typename GT>
@@ -317,12 +386,15 @@ hipError_t sdm_launch_gates(const void* a, const void* b, int dtype, const float
     const int64_t n = (int64_t)B * H * T;
     if (n == 0) return hipSuccess;
     const unsigned blocks = (unsigned)((n + 255) / 256);
-    if (dtype == SDM_DT_BF16)
-        hipLaunchKernelGGL(gates_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, static_cast<const bf16_t*>(a),
+    if (dtype == SDM_DT_BF16) {
+        auto kfn = n >> 31 ? gates_kernel<bf16_t, uint64_t> : gates_kernel<bf16_t, uint32_t>;
+        hipLaunchKernelGGL(kfn, dim3(blocks), dim3(256), 0, st, static_cast<const bf16_t*>(a),
                            static_cast<const bf16_t*>(b), A, bdt, H, T, n, alpha, beta);
-    else
-        hipLaunchKernelGGL(gates_kernel<float>, dim3(blocks), dim3(256), 0, st, static_cast<const float*>(a),
+    } else {
+        auto kfn = n >> 31 ? gates_kernel<float, uint64_t> : gates_kernel<float, uint32_t>;
+        hipLaunchKernelGGL(kfn, dim3(blocks), dim3(256), 0, st, static_cast<const float*>(a),
                            static_cast<const float*>(b), A, bdt, H, T, n, alpha, beta);
+    }
     return hipGetLastError();
 }
 
@@ -364,7 +436,8 @@ hipError_t sdm_launch_norm_gate_bwd(const float* y, const void* g, int g_dtype, 
                                     float* dgamma, float* part, hipStream_t st) {
     if (rows == 0) {   // dgamma = 0: a column sum over no blocks (a kernel, not a memset)
         if (!dgamma) return hipSuccess;
-        hipLaunchKernelGGL(colsum_kernel, dim3((dv + 255) / 256), dim3(256), 0, st, part, 0, dv, dgamma);
+        hipLaunchKernelGGL(colsum_kernel, dim3((dv + CS_COLS - 1) / CS_COLS), dim3(CS_COLS * CS_PARTS), 0, st, part, 0, dv,
+                           dgamma);
         return hipGetLastError();
     }
     hipError_t e = g_dtype == SDM_DT_BF16
@@ -372,6 +445,7 @@ hipError_t sdm_launch_norm_gate_bwd(const float* y, const void* g, int g_dtype, 
                        : launch_ng_bwd_t<float>(y, g, gamma, eps, act, dout, rows, dv, dy, dg, part, st);
     if (e != hipSuccess || !dgamma) return e;
     const int64_t nblk = (int64_t)(sdm_norm_gate_bwd_ws(rows, dv) / (dv * sizeof(float)));
-    hipLaunchKernelGGL(colsum_kernel, dim3((dv + 255) / 256), dim3(256), 0, st, part, (int)nblk, dv, dgamma);
+    hipLaunchKernelGGL(colsum_kernel, dim3((dv + CS_COLS - 1) / CS_COLS), dim3(CS_COLS * CS_PARTS), 0, st, part,
+                       (int)nblk, dv, dgamma);
     return hipGetLastError();
 }
