@@ -1455,14 +1455,18 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE) void decode_kernel(
     const float* __restrict__ gA, const float* __restrict__ gbdt) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int stream = blockIdx.x;
-    if (stream == 0 && threadIdx.x < 4) flags[threadIdx.x] = 0u;   // the call's device-error words
+    // columns [c_beg, c_end) of the stream: each workgroup of a stream finds the slots for itself
+    const int chunks = (dv + DEC_COLS - 1) / DEC_COLS;
+    const int c_beg = (int)(chunks * blockIdx.y / gridDim.y) * DEC_COLS;
+    const int c_end = min(dv, (int)(chunks * (blockIdx.y + 1) / gridDim.y) * DEC_COLS);
+    if (stream == 0 && blockIdx.y == 0 && threadIdx.x < 4) flags[threadIdx.x] = 0u;   // the call's device-error words
     // the two rows' slot lists and weights, past both phases' LDS: [read, write][KM]
     int32_t* sel_id = reinterpret_cast<int32_t*>(smem + decode_sel_offset(E, KM, topk));
     float* sel_val = reinterpret_cast<float*>(sel_id + 2 * KM);
     int* fail = reinterpret_cast<int*>(sel_val + 2 * KM);           // [2] fast stage 1 overflowed, per row
     // the token's gates and its first column chunk of v, loaded before any other work
     float al = load_scalar(alpha, in_dtype, stream), be = load_scalar(beta, in_dtype, stream);
-    const v4f v_first = load_quad(v, in_dtype, (size_t)stream * dv + min((int)(threadIdx.x % 32) * 4, dv - 4));
+    const v4f v_first = load_quad(v, in_dtype, (size_t)stream * dv + min(c_beg + (int)(threadIdx.x % 32) * 4, dv - 4));
     {
         // both rows at once: score rows 0 (read query) and 1 (write key), then
         // phases B, C
@@ -1474,6 +1478,7 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE) void decode_kernel(
         const uint16_t* pairs;
         int ncand;
         tile_pairs<KM>(topk, reinterpret_cast<uint16_t*>(kbufs + AWAVES * SDM_WAVE), pairs, ncand);
+        Entry* scr4 = scratch + 6 * KM;   // past the two rows' scratch and lists: one list per wave
         const size_t hc = (size_t)(stream % H) * 2 * s * (dk / 2);
         bool joint = false;
         if constexpr (MODE == 2 && E <= 4) {
@@ -1502,6 +1507,11 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE) void decode_kernel(
                               lst) && lane_id() == 0)
                 fail[sd] = 1;
             __syncthreads();
+        } else if constexpr (KM <= MAXK) {
+            const int sd = wave >> 1, hf = wave & 1;   // one scratch list per wave
+            half_topk<E>(scores + (sd * 2 + hf) * SP, s, topk, scr4 + wave * KM, kbufs + wave * SDM_WAVE,
+                         scratch + sd * 3 * KM + (1 + hf) * KM);
+            __syncthreads();
         }
         if (wave < 2) {
             int32_t* io = sel_id + wave * KM;
@@ -1516,6 +1526,8 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE) void decode_kernel(
                     wait_lds();
                     __builtin_amdgcn_wave_barrier();
                 }
+            } else if constexpr (KM <= MAXK) {
+                token_pairs(s, topk, ncand, pairs, w.scr, w.listA, w.listB, w.kbuf, io, vo, nullptr);
             } else {
                 select_token<E, KM>(w, row, s, topk, ncand, pairs, io, vo, nullptr);
             }
@@ -1525,7 +1537,7 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE) void decode_kernel(
 
     const int W = topk, R = topk;
     const int tid = threadIdx.x, rg = tid / 32, cq = tid % 32;
-    for (int i = tid; i < 2 * topk; i += blockDim.x) {   // the lists out to the caller
+    for (int i = tid; i < 2 * topk && blockIdx.y == 0; i += blockDim.x) {   // the lists out to the caller
         const int sd = i >= topk, j = i - sd * topk;
         const size_t o = (size_t)stream * topk + j;
         (sd ? w_idx : r_idx)[o] = sel_id[sd * KM + j];
@@ -1553,7 +1565,7 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE) void decode_kernel(
     // the first column chunk's rows, in flight while the links are found
     v4f P[DEC_ROWS], Q[DEC_ROWS];
     {
-        const int cl = min(cq * 4, dv - 4);
+        const int cl = min(c_beg + cq * 4, dv - 4);
 #pragma unroll
         for (int j = 0; j < DEC_ROWS; ++j) {
             const int n = rg + DEC_RG * j;
@@ -1577,11 +1589,11 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE) void decode_kernel(
     }
     sdm_gates_of(gA, gbdt, stream % H, al, be);
 
-    for (int c0 = 0; c0 < dv; c0 += DEC_COLS) {
+    for (int c0 = c_beg; c0 < c_end; c0 += DEC_COLS) {
         const int col = c0 + cq * 4;
         const bool colok = col < dv;      // d_v is a multiple of 4: whole quads
         const int cl = colok ? col : dv - 4;
-        if (c0 > 0) {
+        if (c0 > c_beg) {
 #pragma unroll
             for (int j = 0; j < DEC_ROWS; ++j) {
                 const int n = rg + DEC_RG * j;
@@ -1598,7 +1610,7 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE) void decode_kernel(
         v4f u = v4zero();
 #pragma unroll
         for (int g = 0; g < DEC_RG; ++g) u += ld4(red + g * DEC_COLS + cq * 4);
-        const v4f e = be * ((c0 == 0 ? v_first : load_quad(v, in_dtype, (size_t)stream * dv + cl)) - u);
+        const v4f e = be * ((c0 == c_beg ? v_first : load_quad(v, in_dtype, (size_t)stream * dv + cl)) - u);
 #pragma unroll
         for (int j = 0; j < DEC_ROWS; ++j) {
             const int n = rg + DEC_RG * j;
@@ -1894,6 +1906,11 @@ hipError_t launch_decode_m(const void* q, const void* k, const void* cb_q, const
     const XT* kp = static_cast<const XT*>(k);
     const XT* cq = static_cast<const XT*>(cb_q);
     const XT* ck = static_cast<const XT*>(cb_k);
+    // Workgroups per stream: with fewer streams than two per compute unit and rows
+    // of several 128-column chunks the chunks go to workgroups of their own, each
+    // repeating the selection (the paper's 1.4B layer, 32 streams of d_v = 960: 54 us a layer call, 28 split).
+    const int chunks = (dv + DEC_COLS - 1) / DEC_COLS;
+    const unsigned split = std::max(1, std::min(chunks, sdm_device_simds() / 2 / (B * H)));
 #define SDM_DEC_CASE(EE, KM)                                                                              \
     {                                                                                                     \
         const size_t sm = decode_lds_bytes(EE, KM, topk);                                                  \
@@ -1901,7 +1918,7 @@ hipError_t launch_decode_m(const void* q, const void* k, const void* cb_q, const
         hipError_t e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize,  \
                                            (int)sm);                                                      \
         if (e != hipSuccess) return e;                                                                    \
-        hipLaunchKernelGGL(kfn, dim3(B * H), dim3(AWAVES * SDM_WAVE), sm, st, qp, kp, cq, ck, H, dk, s,   \
+        hipLaunchKernelGGL(kfn, dim3(B * H, split), dim3(AWAVES * SDM_WAVE), sm, st, qp, kp, cq, ck, H, dk, s, \
                            topk, v, alpha, beta, in_dtype, mem, N, dv, r_idx, r_val, w_idx, w_val, y, flags, \
                            gA, gbdt);                                                                     \
         return hipGetLastError();                                                                         \
