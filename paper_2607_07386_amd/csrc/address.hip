@@ -94,7 +94,10 @@ __host__ __device__ constexpr int pair_count(int k) {
 }
 static_assert(pair_count(MAXK_BIG) <= MAXCAND_BIG * SDM_WAVE, "pair counts, k <= 128");
 
-// k-th largest key: the largest tau with #{key >= tau} >= k.
+// A bound that splits off the k largest keys: the largest tau with #{key >= tau}
+// >= k, or, as soon as the bisection meets it, one that exactly k keys reach
+// (without a tie the k-th and the next key differ well before the last bit:
+// about 20 of the 32 steps).
 template <int E>
 __device__ uint32_t kth_key(const uint32_t (&key)[E], int k) {
     uint32_t tau = 0u;
@@ -104,6 +107,7 @@ __device__ uint32_t kth_key(const uint32_t (&key)[E], int k) {
 #pragma unroll
         for (int e = 0; e < E; ++e) cnt += popc64(__ballot(key[e] >= cand));
         if (cnt >= k) tau = cand;
+        if (cnt == k) break;
     }
     return tau;
 }
@@ -717,6 +721,16 @@ __device__ __forceinline__ void tile_pairs(int k, uint16_t* lp, const uint16_t*&
     }
 }
 
+// Four consecutive elements at any element alignment.
+__device__ __forceinline__ v4f ld4_any(const float* p) {
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    const f4u v = *reinterpret_cast<const f4u*>(p);
+    return v4f{v.x, v.y, v.z, v.w};
+}
+__device__ __forceinline__ v4f ld4_any(const bf16_t* p) {
+    return v4f{to_f32(p[0]), to_f32(p[1]), to_f32(p[2]), to_f32(p[3])};
+}
+
 // Phase A: sub-key scores of tokens t0 .. t0 + nt - 1 (nt <= AT) of one
 // stream (xs: its x, token stride dk; cbh: its head's codebook [2][s][dk/2],
 // unused in direct mode) into score rows 0 .. nt-1: row [NH][SP] for halves
@@ -737,17 +751,42 @@ __device__ __forceinline__ void tile_scores(const XT* __restrict__ xs, const XT*
             scores[i] = j >= s ? -INFINITY : to_f32(xs[(size_t)t * dk + half * s + j]);
         }
     } else if constexpr (MODE == 1) {
+        // Plain FMAs, each score one chain over its d_k / 2 terms in order.  A thread
+        // takes one sub-key for TG tokens, so the sub-key rows (a line per lane and
+        // load) are read once per TG tokens; the tokens' values are the same for the
+        // whole wave.  One sub-key and token per thread read a row per score: 206 us
+        // a side for 11,655 tokens at sqrt(N) = 100, d_k = 72, 51 now; 6.4 against 0.25 ms
+        // for 16,384 tokens at sqrt(N) = 512, d_k = 200.
+        constexpr int TG = 8;
         const int dh = dk / 2;
-        for (int i = tid; i < nt * NH * SP; i += blockDim.x) {
-            const int tt = i / (NH * SP), half = HB + (i / SP) % NH, j = i % SP;
-            const int t = t0 + tt;
-            float acc = 0.f;
-            if (j < s) {
-                const XT* xr = xs + (size_t)t * dk + half * dh;
-                const XT* cr = cbh + ((size_t)half * s + j) * dh;
-                for (int c = 0; c < dh; ++c) acc = fmaf(to_f32(xr[c]), to_f32(cr[c]), acc);
+        for (int i = tid; i < (nt + TG - 1) / TG * NH * SP; i += blockDim.x) {
+            const int rest = __builtin_amdgcn_readfirstlane(i / SP), j = i - rest * SP;
+            const int half = HB + rest % NH, tg = rest / NH * TG, n = min(TG, nt - tg);
+            const XT* xr = xs + (size_t)(t0 + tg) * dk + half * dh;
+            const XT* cr = cbh + ((size_t)half * s + min(j, s - 1)) * dh;
+            float acc[TG];
+#pragma unroll
+            for (int u = 0; u < TG; ++u) acc[u] = 0.f;
+            int c = 0;
+            for (; c + 4 <= dh; c += 4) {
+                const v4f b = ld4_any(cr + c);
+#pragma unroll
+                for (int u = 0; u < TG; ++u) {
+                    const v4f a = ld4_any(xr + (size_t)min(u, n - 1) * dk + c);
+                    acc[u] = fmaf(a.x, b.x, acc[u]);
+                    acc[u] = fmaf(a.y, b.y, acc[u]);
+                    acc[u] = fmaf(a.z, b.z, acc[u]);
+                    acc[u] = fmaf(a.w, b.w, acc[u]);
+                }
             }
-            scores[i] = j < s ? acc : -INFINITY;
+            for (; c < dh; ++c) {
+                const float b = to_f32(cr[c]);
+#pragma unroll
+                for (int u = 0; u < TG; ++u) acc[u] = fmaf(to_f32(xr[(size_t)min(u, n - 1) * dk + c]), b, acc[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < TG; ++u)
+                if (u < n) scores[((tg + u) * NH + half - HB) * SP + j] = j < s ? acc[u] : -INFINITY;
         }
     } else {
         // MFMA 16x16x32: A[i][kk] = x[t0+i][half*dh + kk], B[kk][j] = cb[half][j0+j][kk].
