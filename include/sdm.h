@@ -214,7 +214,9 @@ size_t sdm_forward_noalloc_max_bytes(void);
  * before later work on `stream` when the call returns.  Results equal
  * sdm_scan_fwd's up to the rounding of the reassociated sums and of the
  * triangular solve (and may vary in the last bits between runs: see
- * sdm_set_chunk_scan_cols).
+ * sdm_set_chunk_scan_cols).  With automatic columns, tables large enough that
+ * tokens in flight share few slots are scanned token by token instead (in
+ * rounds, as sdm_scan_fwd with few streams; reproducible), when that is faster.
  *   Arguments as for sdm_scan_fwd, without the undo log; workspace of at least
  *   sdm_scan_fwd_chunked_workspace_bytes() bytes (256-B aligned), which holds
  *   about (8 C^2 + 4 C (W + R) + 40 C W) bytes per stream and chunk (C = 64).
@@ -231,7 +233,8 @@ size_t sdm_scan_fwd_chunked_workspace_bytes(int B, int H, int T, int W, int R);
 /* Columns per workgroup of sdm_scan_fwd_chunked's scan kernel: 8 (the narrow
  * kernel: 16 workgroups per 128-column stream, which fill the chip at few
  * streams; needs d_v % 8 == 0), 16 or 32 (a 128-byte piece of every row), or
- * 0 (the default): 8 when d_v % 8 == 0, W <= 32 and the narrow workgroups
+ * 0 (the default): the scan in rounds of tokens where it is faster (large
+ * tables), else 8 when d_v % 8 == 0, W <= 32 and the narrow workgroups
  * (B H d_v / 8) fit the device at one per compute unit, else 32.
  * Process-wide; any other value returns SDM_ERR_INVALID_ARG and keeps the
  * setting.  The coefficient kernel adds the pair terms of its triangular

@@ -40,7 +40,7 @@ __device__ __forceinline__ int hash_slot(int slot, int bits) {
 
 __device__ __forceinline__ int clamp_slot(int s, int64_t N, unsigned int& bad) {
     if (s < 0 || s >= N) {
-        bad = 1u;
+        bad |= 1u;
         return 0;
     }
     return s;
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(THREADS) void fwd_prep_kernel(
     const float* __restrict__ r_val, const void* __restrict__ alpha, const void* __restrict__ beta, int in_dtype,
     int T, int ta, int te, int W, int R, int64_t N, unsigned char* __restrict__ recs,
     unsigned int* __restrict__ err, const float* __restrict__ gA, const float* __restrict__ gbdt, int H, int pt,
-    int per_log2, int depth, int bits) {
+    int per_log2, int depth, int bits, int positive) {
     extern __shared__ __align__(16) int sm[];
     const FwdRec L = fwd_rec_layout(W, R);
     const int stream = blockIdx.y;
@@ -151,6 +151,7 @@ __global__ __launch_bounds__(THREADS) void fwd_prep_kernel(
                 float al, be;
                 load_gates(alpha, beta, in_dtype, tok, al, be);
                 sdm_gates_of(gA, gbdt, stream % H, al, be);
+                if (positive) al = fmaxf(al, 1e-30f);
                 rho *= al;
                 atomicOr(&omask[tl * MW + m / 32], 1u << (m % 32));
             }
@@ -166,6 +167,10 @@ __global__ __launch_bounds__(THREADS) void fwd_prep_kernel(
         float al, be;
         load_gates(alpha, beta, in_dtype, tok, al, be);
         sdm_gates_of(gA, gbdt, stream % H, al, be);
+        if (positive) {
+            if (!(al > 0.f)) bad |= 2u;
+            al = fmaxf(al, 1e-30f);
+        }
         // yc: rho kappa_n summed over the (rare) read rows of slots the token writes, in row order
         const int own = (lead + tl) * W;
         float yc = 0.f;
@@ -187,7 +192,7 @@ __global__ __launch_bounds__(THREADS) void fwd_prep_kernel(
         if (nrow & 1) reinterpret_cast<short*>(rec + L.off_link)[nrow] = -1;
         for (int o = L.off_ab + 12; o < L.bytes; o += 4) *reinterpret_cast<int*>(rec + o) = 0;
     }
-    if (bad) atomicOr(err, 1u);
+    if (bad) atomicOr(err, bad);
 }
 
 // ---------------------------------------------------------------- backward
@@ -305,7 +310,8 @@ hipError_t sdm_launch_fwd_prep(const ScanFwdArgs& a, int per_log2, int depth, hi
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fwd_prep_kernel, grid, dim3(THREADS), sm, st, a.w_idx, a.w_val, a.r_idx, a.r_val, a.alpha,
                        a.beta, a.in_dtype, a.T, a.tb, a.te, a.W, a.R, a.N, a.ws + SDM_WS_HEADER,
-                       reinterpret_cast<unsigned int*>(a.ws), a.gate_A, a.gate_bdt, a.H, pt, per_log2, depth, bits);
+                       reinterpret_cast<unsigned int*>(a.ws), a.gate_A, a.gate_bdt, a.H, pt, per_log2, depth, bits,
+                       (int)a.positive_gates);
     return hipGetLastError();
 }
 

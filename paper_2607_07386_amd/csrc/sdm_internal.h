@@ -103,6 +103,10 @@ struct ScanFwdArgs {
     // are formed per token (A, b_dt per head, fp32).
     const float* gate_A = nullptr;
     const float* gate_bdt = nullptr;
+    // Forget gates must be positive (the chunk form's decays are logarithms): others,
+    // and those below 1e-30, are taken as 1e-30, and gates <= 0 flagged (bit 1 of
+    // the error word) when the records are made.
+    bool positive_gates = false;
 };
 hipError_t sdm_launch_scan_fwd(const ScanFwdArgs& a, hipStream_t st);   // prep + scan
 size_t sdm_fwd_scan_lds(const ScanFwdArgs& a);   // LDS of one workgroup of that scan

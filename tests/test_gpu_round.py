@@ -80,3 +80,37 @@ def test_round_scan_stages_and_helpers():
         out.append((o["y"], mem))
     for y, mem in out[1:]:
         assert torch.equal(y, out[0][0]) and torch.equal(mem, out[0][1])
+
+
+@pytest.mark.parametrize("T", [130, 2100])
+def test_chunked_call_in_rounds(T):
+    """sdm_scan_fwd_chunked on a table large enough for the scan in rounds (one range,
+    and eight ranges with a ragged end): the oracle's recurrence, with forget gates of
+    zero and below taken as 1e-30 and flagged, as the chunk form does."""
+    S, N, W, dv = 2, 20480, 32, 32
+    rng = np.random.default_rng(T)
+    wi = np.sort(rng.integers(0, N // W, (S, T, W)) + np.arange(W) * (N // W), -1).astype(np.int32)
+    ri = np.where(rng.random((S, T, W)) < 0.3, wi, np.roll(wi, 1, axis=1)).astype(np.int32)
+    wv, rv = (rng.random((S, T, W)) / 8).astype(np.float32), rng.random((S, T, W)).astype(np.float32)
+    v, be = rng.standard_normal((S, T, dv)).astype(np.float32), rng.random((S, T)).astype(np.float32)
+    al = rng.uniform(0.1, 1, (S, T)).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a))[:, None].to(DEV)
+    ws = sdm.chunked_workspace(S, 1, T, W, W, DEV)
+    for bad in (False, True):
+        if bad:
+            al[0, 40], al[1, 77] = 0.0, -0.5
+        mem, memo = torch.zeros((S, 1, N, dv), device=DEV), np.zeros((S, N, dv))
+        sdm.profile_enable(True)
+        y = sdm.scan_fwd_chunked(dev(wi), dev(wv), dev(ri), dev(rv), dev(v), dev(al), dev(be), mem, workspace=ws)
+        torch.cuda.synchronize()
+        assert sdm.profile_read("chunk_scan")[1] == 0 and sdm.profile_read("fwd_scan")[1] == (8 if T > 2047 else 1)
+        sdm.profile_enable(False)
+        yo = oracle.scan_fwd(wi, wv, ri, rv, v, np.maximum(al, 1e-30), be, memo)
+        assert rel_err(y[:, 0].cpu().numpy(), yo) <= REGRESSION_TOL
+        assert rel_err(mem[:, 0].cpu().numpy(), memo) <= REGRESSION_TOL
+        if bad:
+            with pytest.raises(sdm.SdmError) as e:
+                sdm.check_device_errors(ws)
+            assert e.value.status == -5 and "alpha" in str(e.value)
+        else:
+            sdm.check_device_errors(ws)
