@@ -30,6 +30,30 @@
 
 namespace {
 
+// The second side of a launch for both sides (grid z = 2; same sizes, types and
+// kernel instance), or unused.
+struct AddressSide {
+    const void* x;
+    const void* cb;
+    int k;
+    int32_t* idx;
+    float* val;
+};
+// This block's side, and the call's device-error words cleared by the first block.
+template <typename XT>
+__device__ __forceinline__ void address_side(const XT* __restrict__& x, const XT* __restrict__& cb, int& k,
+                                             int32_t* __restrict__& idx, float* __restrict__& val,
+                                             const AddressSide& o, unsigned int* flags) {
+    if (blockIdx.z) {
+        x = static_cast<const XT*>(o.x);
+        cb = static_cast<const XT*>(o.cb);
+        k = o.k;
+        idx = o.idx;
+        val = o.val;
+    }
+    if (flags && threadIdx.x < 4 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) flags[threadIdx.x] = 0u;
+}
+
 constexpr int ATILE = 16;     // tokens per workgroup (the MFMA tile's rows), sqrt(N) <= 256
 // Tokens per workgroup for E = ceil(sqrt(N) / 64): the scores of a tile take
 // 2 AT 64 E floats of LDS, so larger sqrt(N) takes fewer tokens per workgroup
@@ -1302,7 +1326,9 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE, 3) void address_reg_kernel(const
                                                                         int tb, int te, int dk, int s, int k,
                                                                         int32_t* __restrict__ idx,
                                                                         float* __restrict__ val,
-                                                                        float* __restrict__ score) {
+                                                                        float* __restrict__ score,
+                                                                        AddressSide other, unsigned int* flags) {
+    address_side(x, cb, k, idx, val, other, flags);
     using L = RegTile<E, RT>;
     constexpr int NU = L::TOK / AWAVES;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -1350,7 +1376,9 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE) void address_kernel(const XT* __
                                                                     int tb, int te, int dk, int s, int k,
                                                                     int32_t* __restrict__ idx,
                                                                     float* __restrict__ val,
-                                                                    float* __restrict__ score) {
+                                                                    float* __restrict__ score, AddressSide other,
+                                                                    unsigned int* flags) {
+    address_side(x, cb, k, idx, val, other, flags);
     extern __shared__ __align__(16) unsigned char smem[];
     if constexpr (half_seq<E, KM>())
         address_tile_halves<XT, MODE, E, KM>(x, cb, H, T, blockIdx.y, tb + blockIdx.x * tile_tokens<E, KM>(), te, dk,
@@ -1794,22 +1822,23 @@ constexpr size_t tile_lds_bytes() {
 // scores take 4 E registers per lane).
 template <int E>
 hipError_t launch_address_reg(const void* x, const void* cb, int B, int H, int T, int tb, int tn, int dk, int s,
-                              int k, int32_t* idx, float* val, float* score, hipStream_t st) {
+                              int k, int32_t* idx, float* val, float* score, hipStream_t st, const AddressSide* two,
+                              unsigned int* flags) {
     constexpr int RT = 1;
     using L = RegTile<E, RT>;
     auto kfn = address_reg_kernel<E, RT>;
     hipError_t e = hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)L::BYTES);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kfn, dim3((tn + L::TOK - 1) / L::TOK, B * H), dim3(AWAVES * SDM_WAVE), L::BYTES, st,
+    hipLaunchKernelGGL(kfn, dim3((tn + L::TOK - 1) / L::TOK, B * H, two ? 2 : 1), dim3(AWAVES * SDM_WAVE), L::BYTES, st,
                        static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(cb), H, T, tb, tb + tn, dk, s, k,
-                       idx, val, score);
+                       idx, val, score, two ? *two : AddressSide{}, flags);
     return hipGetLastError();
 }
 
 template <typename XT, int MODE>
 hipError_t launch_address_e(const void* x, const void* cb, int B, int H, int T, int tb, int tn, int dk,
                             int s, int k, int32_t* idx, float* val, float* score, hipStream_t st,
-                            size_t lds_free) {
+                            size_t lds_free, const AddressSide* two, unsigned int* flags) {
     const int E = (s + SDM_WAVE - 1) / SDM_WAVE;
     if constexpr (MODE == 2) {
         // bf16 codebooks, sqrt(N) in (256, 1024], d_k / 2 <= 64, k <= 32:
@@ -1818,8 +1847,9 @@ hipError_t launch_address_e(const void* x, const void* cb, int B, int H, int T, 
         // sqrt(N) = 256 the LDS tile stays: 0.87 ms per side (B=8 H=16
         // T=4096) against 1.04 for 32-token register tiles.
         if (E > 4 && E <= 16 && dk / 2 <= 64 && k <= 32 && k <= s) {
-            if (E <= 8) return launch_address_reg<8>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st);
-            return launch_address_reg<16>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st);
+            if (E <= 8)
+                return launch_address_reg<8>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, two, flags);
+            return launch_address_reg<16>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, two, flags);
         }
     }
     const XT* xp = static_cast<const XT*>(x);
@@ -1846,8 +1876,8 @@ hipError_t launch_address_e(const void* x, const void* cb, int B, int H, int T, 
         hipError_t e = hipFuncSetAttribute((const void*)kfn,                                    \
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)sm); \
         if (e != hipSuccess) return e;                                                          \
-        hipLaunchKernelGGL(kfn, dim3((tn + AT - 1) / AT, B * H), dim3(AWAVES * SDM_WAVE), sm, st, xp, cp, \
-                           H, T, tb, tb + tn, dk, s, k, idx, val, score);                      \
+        hipLaunchKernelGGL(kfn, dim3((tn + AT - 1) / AT, B * H, two ? 2 : 1), dim3(AWAVES * SDM_WAVE), sm, st, \
+                           xp, cp, H, T, tb, tb + tn, dk, s, k, idx, val, score, two ? *two : AddressSide{}, flags); \
         return hipGetLastError();                                                               \
     }
     if (k > MAXK) {   // k <= sqrt(N), so E >= 2
@@ -1866,18 +1896,42 @@ hipError_t launch_address_e(const void* x, const void* cb, int B, int H, int T, 
 
 }  // namespace
 
+namespace {
+hipError_t launch_address_any(const void* x, int x_dtype, const void* cb, int B, int H, int T, int tb, int tn, int dk,
+                              int s, int k, int32_t* idx, float* val, float* score, hipStream_t st, size_t lds_free,
+                              const AddressSide* two, unsigned int* flags) {
+    if (tn <= 0) return hipSuccess;
+    if (x_dtype == SDM_DT_BF16) {
+        if (!cb)
+            return launch_address_e<bf16_t, 0>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free, two, flags);
+        if ((dk / 2) % 8 == 0)
+            return launch_address_e<bf16_t, 2>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free, two, flags);
+        return launch_address_e<bf16_t, 1>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free, two, flags);
+    }
+    if (!cb)
+        return launch_address_e<float, 0>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free, two, flags);
+    return launch_address_e<float, 1>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free, two, flags);
+}
+}  // namespace
+
 hipError_t sdm_launch_address(const void* x, int x_dtype, const void* cb, int B, int H, int T,
                               int tb, int tn, int dk, int s, int k, int32_t* idx, float* val,
                               float* score, hipStream_t st, size_t lds_free) {
-    if (tn <= 0) return hipSuccess;
-    if (x_dtype == SDM_DT_BF16) {
-        if (!cb) return launch_address_e<bf16_t, 0>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free);
-        if ((dk / 2) % 8 == 0)
-            return launch_address_e<bf16_t, 2>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free);
-        return launch_address_e<bf16_t, 1>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free);
-    }
-    if (!cb) return launch_address_e<float, 0>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free);
-    return launch_address_e<float, 1>(x, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free);
+    return launch_address_any(x, x_dtype, cb, B, H, T, tb, tn, dk, s, k, idx, val, score, st, lds_free, nullptr,
+                              nullptr);
+}
+
+// Both sides by one kernel instance: the same addressing mode, and list lengths on
+// the same side of the limits by which launch_address_e chooses (32, 64).
+bool sdm_address_joint_ok(const void* cb_q, const void* cb_k, int R, int W) {
+    return (cb_q == nullptr) == (cb_k == nullptr) && (R > MAXK) == (W > MAXK) && (R > 32) == (W > 32);
+}
+
+hipError_t sdm_launch_address_joint(const void* q, const void* k, int x_dtype, const void* cb_q, const void* cb_k,
+                                    int B, int H, int T, int tn, int dk, int s, int R, int W, int32_t* r_idx,
+                                    float* r_val, int32_t* w_idx, float* w_val, unsigned int* flags, hipStream_t st) {
+    const AddressSide two{k, cb_k, W, w_idx, w_val};
+    return launch_address_any(q, x_dtype, cb_q, B, H, T, 0, tn, dk, s, R, r_idx, r_val, nullptr, st, 0, &two, flags);
 }
 
 namespace {

@@ -595,7 +595,13 @@ int sdm_forward_impl(const void* q, const void* k, int x_dtype, const void* cb_q
     }
     auto stage_begin = [&](int c) { return c == 0 ? 0 : std::min(T, first + (c - 1) * len); };
 
-    hipError_t e = sdm_launch_zero_words(workspace, 4, st);
+    // A first stage that runs alone takes both sides in one launch, which also clears
+    // the error words: the two launches of a short prefill (2 x 16 streams of 509
+    // tokens) took 42 us each, 75 together; of a tiny one (256 fp32 tokens, two heads)
+    // 22 us each, 22 together.  Beside a scan (later stages)
+    // the sides stay separate.
+    const bool joint = sdm_address_joint_ok(cb_q, cb_k, R, W);
+    hipError_t e = joint ? hipSuccess : sdm_launch_zero_words(workspace, 4, st);
     if (e != hipSuccess) return hip_fail(e, "sdm_forward flag reset");
     ScanFwdArgs a;
     a.w_idx = w_idx; a.w_val = w_val; a.r_idx = r_idx; a.r_val = r_val;
@@ -608,6 +614,18 @@ int sdm_forward_impl(const void* q, const void* k, int x_dtype, const void* cb_q
     // the rest of every CU's LDS
     auto stage_front = [&](int tb, int te, hipStream_t sx, size_t lds_free) -> hipError_t {
         hipError_t ee;
+        if (joint && tb == 0) {
+            {
+                SdmProfScope ps(SDM_K_ADDRESS, sx);
+                ee = sdm_launch_address_joint(q, k, x_dtype, cb_q, cb_k, B, H, T, te, d_k, s, R, W, r_idx, r_val, w_idx,
+                                              w_val, static_cast<unsigned int*>(workspace), sx);
+            }
+            if (ee != hipSuccess) return ee;
+            ScanFwdArgs ac = a;
+            ac.tb = tb;
+            ac.te = te;
+            return sdm_launch_fwd_prep_range(ac, sx);
+        }
         {
             SdmProfScope ps(SDM_K_ADDRESS, sx);
             ee = sdm_launch_address(q, x_dtype, cb_q, B, H, T, tb, te - tb, d_k, s, R, r_idx, r_val,

@@ -69,6 +69,13 @@ __host__ __device__ inline BwdRec bwd_rec_layout(int W, int R) {
 hipError_t sdm_launch_address(const void* x, int x_dtype, const void* cb, int B, int H, int T,
                               int tb, int tn, int dk, int s, int k, int32_t* idx, float* val,
                               float* score, hipStream_t st, size_t lds_free = 0);
+// Tokens [0, tn) of both sides (q with cb_q, R reads; k with cb_k, W writes) in one
+// launch, which also clears the four error words at `flags`; for sides that
+// sdm_address_joint_ok says take the same kernel.
+bool sdm_address_joint_ok(const void* cb_q, const void* cb_k, int R, int W);
+hipError_t sdm_launch_address_joint(const void* q, const void* k, int x_dtype, const void* cb_q, const void* cb_k,
+                                    int B, int H, int T, int tn, int dk, int s, int R, int W, int32_t* r_idx,
+                                    float* r_val, int32_t* w_idx, float* w_val, unsigned int* flags, hipStream_t st);
 // token-sides (b, h, t) for t in [tb, tb + tn)
 // One token per stream (T = 1, no undo log): addressing of both sides and the
 // scan step in one launch, one workgroup per stream.  cb_q and cb_k are both
