@@ -769,7 +769,7 @@ int scan_bwd_impl(const void* cb_q, const void* cb_k, int cb_dtype, int d_k, con
     a.ws = ws;
     a.gate_A = gA;
     a.gate_bdt = gbdt;
-    a.line = sdm_bwd_line_io(a) ? 1 : 0;   // one decision for every stage and the reduce
+    a.line = sdm_bwd_line_io(a);   // one decision for every stage and the reduce
 
     // Stages of tokens from the end of the sequence down: a short first stage,
     // then stages of len = max(chunk, T/4) tokens (multiples of 64, at most

@@ -932,22 +932,35 @@ bool sdm_bwd_plan_ok(int W, int R, int dv, int in_dtype) {
     return bwd_plan_sw<BSW_MIN>(W, R, dv, in_dtype, &p);
 }
 
-bool sdm_bwd_line_io(const ScanBwdArgs& a) {
+int sdm_bwd_line_io(const ScanBwdArgs& a) {
+    if (sdm_bwd_round(a)) return 2;
     BwdPlan plan;
     return bwd_plan(a.B * a.H, a.W, a.R, a.dv, a.in_dtype, &plan) && line_io_ok(a, plan);
 }
 
+namespace {
+bool in_rounds(const ScanBwdArgs& a) { return a.line == 2 || (a.line < 0 && sdm_bwd_round(a)); }
+}  // namespace
+
 hipError_t sdm_launch_bwd_prep_range(const ScanBwdArgs& a, hipStream_t st) {
+    if (in_rounds(a)) {
+        SdmProfScope ps(SDM_K_BWD_PREP, st);
+        return sdm_launch_bwd_round_prep(a, st);
+    }
     BwdPlan plan;   // the links' window is the scan's prefetch depth
     if (!bwd_plan(a.B * a.H, a.W, a.R, a.dv, a.in_dtype, &plan)) return hipErrorInvalidConfiguration;
     bool ok;
     const bool line = use_line(a, plan, &ok);
     if (!ok) return hipErrorInvalidConfiguration;
     SdmProfScope ps(SDM_K_BWD_PREP, st);
-    return sdm_launch_bwd_prep(a, line ? line_pd(a) : plan.PD, st);
+    return sdm_launch_bwd_prep(a, 0, (line ? line_pd(a) : plan.PD) - 1, st);
 }
 
 hipError_t sdm_launch_bwd_scan_range(const ScanBwdArgs& a, hipStream_t st) {
+    if (in_rounds(a)) {
+        SdmProfScope ps(SDM_K_BWD_SCAN, st);
+        return sdm_launch_bwd_round(a, reinterpret_cast<float*>(a.ws + bwd_part_offset(a.B, a.H, a.T, a.W, a.R)), st);
+    }
     BwdPlan plan;
     if (!bwd_plan(a.B * a.H, a.W, a.R, a.dv, a.in_dtype, &plan)) return hipErrorInvalidConfiguration;
     bool ok;
@@ -960,12 +973,17 @@ hipError_t sdm_launch_bwd_scan_range(const ScanBwdArgs& a, hipStream_t st) {
 }
 
 hipError_t sdm_launch_bwd_reduce_range(const ScanBwdArgs& a, hipStream_t st) {
-    BwdPlan plan;
-    if (!bwd_plan(a.B * a.H, a.W, a.R, a.dv, a.in_dtype, &plan)) return hipErrorInvalidConfiguration;
-    bool ok;
-    const bool line = use_line(a, plan, &ok);
-    if (!ok) return hipErrorInvalidConfiguration;
-    const int n_parts = line ? a.dv / 32 : plan.n_slices;   // partial sums per (stream, token)
+    int n_parts;   // partial sums per (stream, token)
+    if (in_rounds(a)) {
+        n_parts = sdm_bwd_round_parts(a);
+    } else {
+        BwdPlan plan;
+        if (!bwd_plan(a.B * a.H, a.W, a.R, a.dv, a.in_dtype, &plan)) return hipErrorInvalidConfiguration;
+        bool ok;
+        const bool line = use_line(a, plan, &ok);
+        if (!ok) return hipErrorInvalidConfiguration;
+        n_parts = line ? a.dv / 32 : plan.n_slices;
+    }
     const float* part = reinterpret_cast<const float*>(a.ws + bwd_part_offset(a.B, a.H, a.T, a.W, a.R));
     const int S = a.B * a.H, n = a.te - a.tb;
     if (S == 0 || n <= 0) return hipSuccess;

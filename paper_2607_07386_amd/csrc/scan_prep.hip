@@ -197,7 +197,8 @@ __global__ __launch_bounds__(THREADS) void fwd_prep_kernel(
 
 // ---------------------------------------------------------------- backward
 // The backward visits t = T-1 .. 0.  For token t:
-//  lm[m]  (M_t[j_m]): the earliest later writer t+d, 1 <= d < PD, whose undo
+//  lm[m]  (M_t[j_m]): the earliest later writer t+d inside the window (d < PD;
+//         in rounds, those of its own round and `depth` rounds before) whose undo
 //         restored the row; entry n = its write position.
 //  lgr[m] (G[j_m]) and lgw[n] (G[i_n]): the earliest later token t+d that
 //         changed the adjoint row, either by its write adjoint (entry R + n,
@@ -211,7 +212,7 @@ __global__ __launch_bounds__(THREADS) void bwd_prep_kernel(
     const float* __restrict__ r_val, const void* __restrict__ alpha, const void* __restrict__ beta, int in_dtype,
     int T, int tb, int te, int W, int R, int64_t N, unsigned char* __restrict__ recs,
     unsigned int* __restrict__ err, const float* __restrict__ gA, const float* __restrict__ gbdt, int H, int pt,
-    int pd, int bits) {
+    int per_log2, int depth, int bits) {
     // records of tokens [tb, te); links only to tokens below te (the backward
     // of later tokens, in an earlier call, left its rows in HBM)
     extern __shared__ __align__(16) int sm[];
@@ -219,11 +220,12 @@ __global__ __launch_bounds__(THREADS) void bwd_prep_kernel(
     const int stream = blockIdx.y;
     const int t0 = tb + blockIdx.x * pt;
     const int ntok = min(pt, te - t0);
-    const int span = min(pt + pd - 1, te - t0);   // tokens t0 .. t0+span-1 (later ones included)
+    const int per = 1 << per_log2, reach = (depth + 1) * per - 1;   // tokens that a link can span
+    const int span = min(pt + reach, te - t0);   // tokens t0 .. t0+span-1 (later ones included)
     const int nrow = W + R, nlink = 2 * R + W;
     int* head = sm;                                                    // [1 << bits]
-    int* sl = head + (1 << bits);                                      // [pt + pd - 1][W + R]
-    short* nxt = reinterpret_cast<short*>(sl + (pt + pd - 1) * nrow);   // [pt + pd - 1][W + R]
+    int* sl = head + (1 << bits);                                      // [pt + reach][W + R]
+    short* nxt = reinterpret_cast<short*>(sl + (pt + reach) * nrow);   // [pt + reach][W + R]
     const size_t sbase = (size_t)stream * T;
     unsigned int bad = 0u;
 
@@ -246,7 +248,9 @@ __global__ __launch_bounds__(THREADS) void bwd_prep_kernel(
         unsigned char* rec = recs + tok * L.bytes;
         const int slot = sl[i];
         const float wt = wrow ? w_val[tok * W + r] : r_val[tok * R + r - W];
-        const int own = tl * nrow, later = own + nrow, end = min(span, tl + pd) * nrow;
+        const int own = tl * nrow, later = own + nrow;
+        // the last token it links to: the start of the round `depth` rounds before its own
+        const int end = min(span, tl + depth * per + ((te - 1 - (t0 + tl)) & (per - 1)) + 1) * nrow;
         int g = end, w = end, self = later;
         for (int e = head[hash_slot(slot, bits)]; e >= 0; e = nxt[e]) {
             if (sl[e] != slot) continue;
@@ -315,11 +319,12 @@ hipError_t sdm_launch_fwd_prep(const ScanFwdArgs& a, int per_log2, int depth, hi
     return hipGetLastError();
 }
 
-// Records of the backward's tokens [a.tb, a.te), linked over pd tokens.
-hipError_t sdm_launch_bwd_prep(const ScanBwdArgs& a, int pd, hipStream_t st) {
+// Records of the backward's tokens [a.tb, a.te) for a scan that takes 1 << per_log2
+// tokens a round, counted from te down, and keeps `depth` rounds in flight.
+hipError_t sdm_launch_bwd_prep(const ScanBwdArgs& a, int per_log2, int depth, hipStream_t st) {
     const int S = a.B * a.H;
     const int pt = prep_tokens(a.W + a.R);
-    const int n = (pt + pd - 1) * (a.W + a.R);
+    const int n = (pt + ((depth + 1) << per_log2) - 1) * (a.W + a.R);
     const int bits = hash_bits(n);
     dim3 grid((a.te - a.tb + pt - 1) / pt, S);
     const size_t sm = sizeof(int) * (((size_t)1 << bits) + n) + sizeof(short) * (size_t)n;
@@ -327,7 +332,7 @@ hipError_t sdm_launch_bwd_prep(const ScanBwdArgs& a, int pd, hipStream_t st) {
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(bwd_prep_kernel, grid, dim3(THREADS), sm, st, a.w_idx, a.w_val, a.r_idx, a.r_val, a.alpha,
                        a.beta, a.in_dtype, a.T, a.tb, a.te, a.W, a.R, a.N, a.ws + SDM_WS_HEADER,
-                       reinterpret_cast<unsigned int*>(a.ws), a.gate_A, a.gate_bdt, a.H, pt, pd, bits);
+                       reinterpret_cast<unsigned int*>(a.ws), a.gate_A, a.gate_bdt, a.H, pt, per_log2, depth, bits);
     return hipGetLastError();
 }
 

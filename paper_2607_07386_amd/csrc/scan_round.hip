@@ -42,15 +42,14 @@
 #include "sdm_common.h"
 #include "sdm_internal.h"
 #include "sdm_reduce.h"
+#include "sdm_round.h"
 #include "sdm.h"
 
 namespace {
 
-constexpr int CW = 32;              // columns per workgroup: one 128-byte line
-constexpr int CQ = CW / 4;          // lanes per row
-constexpr int RG = SDM_WAVE / CQ;   // row groups: rows rg K .. rg K + K - 1 per lane
+constexpr int CW = RND_CW, CQ = RND_CQ, RG = RND_RG;
+constexpr uint32_t OOB = RND_OOB;
 constexpr int LDS_LIMIT = 160 * 1024;
-constexpr uint32_t OOB = 0x80000000u;   // past every table (below 2 GiB): loads give 0, stores are dropped
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -68,58 +67,6 @@ struct RoundGeom {
 __host__ __device__ inline int round_lds(int nwv, int nrec, int ring, int rec_bytes, int W) {
     return 64 + nwv * nrec * rec_bytes + ring * W * CW * 4;
 }
-
-template <int K, bool EX>
-struct RoundLane {
-    int rg, cq;
-    uint32_t dv4, lc4;      // row pitch and this lane's column offset, bytes
-    bool colok;
-
-    __device__ __forceinline__ uint32_t off(int slot, bool ok) const {
-        const uint32_t o = __umul24((uint32_t)slot, dv4) + lc4;
-        return EX ? o : (ok && colok ? o : OOB);
-    }
-    // K consecutive 32-bit words of a list of n starting at row rg K (EX: n = 8 K, 16-byte aligned)
-    __device__ __forceinline__ void words(const unsigned char* list, int n, int (&out)[K]) const {
-        if constexpr (EX && K % 4 == 0) {
-#pragma unroll
-            for (int j = 0; j < K / 4; ++j) {
-                const u4v x = *reinterpret_cast<const u4v*>(list + (rg * K + 4 * j) * 4);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) out[4 * j + i] = (int)x[i];
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < K; ++k) out[k] = reinterpret_cast<const int*>(list)[min(rg * K + k, n - 1)];
-        }
-    }
-    __device__ __forceinline__ void floats(const unsigned char* list, int n, float (&out)[K]) const {
-        int x[K];
-        words(list, n, x);
-#pragma unroll
-        for (int k = 0; k < K; ++k) out[k] = (EX || rg * K + k < n) ? __int_as_float(x[k]) : 0.f;
-    }
-    __device__ __forceinline__ void links(const unsigned char* list, int n, int (&out)[K]) const {
-        if constexpr (EX && K % 4 == 0) {
-#pragma unroll
-            for (int j = 0; j < K / 4; ++j) {
-                const u2v x = *reinterpret_cast<const u2v*>(list + (rg * K + 4 * j) * 2);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    out[4 * j + 2 * i] = (int)(short)(x[i] & 0xffffu);
-                    out[4 * j + 2 * i + 1] = (int)x[i] >> 16;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int n0 = rg * K + k;
-                out[k] = reinterpret_cast<const short*>(list)[min(n0, n - 1)];
-                if (n0 >= n) out[k] = -1;
-            }
-        }
-    }
-};
 
 // A helper workgroup: touches one word of every line that its main workgroup
 // will load, for tokens at most `lead` past those the main workgroup has done

@@ -180,7 +180,7 @@ struct ScanBwdArgs {
     float* dr_val;    // [B,H,T,R]
     unsigned char* ws;
     int tb = 0, te = 0;  // tokens processed, te-1 down to tb (layout strides use T)
-    int line = -1;       // line-cooperative kernel: 1 / 0, or -1 to decide from the shape
+    int line = -1;       // kernel: 2 in rounds, 1 line-cooperative, 0 per wave, or -1 to decide from the shape
     const float* gate_A = nullptr;     // as in ScanFwdArgs: alpha, beta are pre-activations
     const float* gate_bdt = nullptr;
 };
@@ -190,9 +190,18 @@ struct ScanBwdArgs {
 hipError_t sdm_launch_bwd_prep_range(const ScanBwdArgs& a, hipStream_t st);
 hipError_t sdm_launch_bwd_scan_range(const ScanBwdArgs& a, hipStream_t st);
 hipError_t sdm_launch_bwd_reduce_range(const ScanBwdArgs& a, hipStream_t st);
-// whether the backward of this shape runs the line-cooperative kernel now
-bool sdm_bwd_line_io(const ScanBwdArgs& a);
-hipError_t sdm_launch_bwd_prep(const ScanBwdArgs& a, int pd, hipStream_t st);
+// the kernel (ScanBwdArgs::line) that the backward of this shape runs now
+int sdm_bwd_line_io(const ScanBwdArgs& a);
+// Records of the backward's tokens [a.tb, a.te) for a scan that takes 1 << per_log2
+// tokens a round, counted from te down, with `depth` rounds in flight (0 and PD -
+// 1: token by token with PD tokens in flight).
+hipError_t sdm_launch_bwd_prep(const ScanBwdArgs& a, int per_log2, int depth, hipStream_t st);
+// The backward in rounds of tokens (scan_bwd_round.hip): whether these arguments
+// take it, its partial sums per (stream, token), its records and its scan.
+bool sdm_bwd_round(const ScanBwdArgs& a);
+int sdm_bwd_round_parts(const ScanBwdArgs& a);
+hipError_t sdm_launch_bwd_round_prep(const ScanBwdArgs& a, hipStream_t st);
+hipError_t sdm_launch_bwd_round(const ScanBwdArgs& a, float* part, hipStream_t st);
 bool sdm_bwd_plan_ok(int W, int R, int dv, int in_dtype);
 size_t sdm_bwd_ws_bytes(int B, int H, int T, int W, int R, int dv);
 

@@ -114,3 +114,41 @@ def test_chunked_call_in_rounds(T):
             assert e.value.status == -5 and "alpha" in str(e.value)
         else:
             sdm.check_device_errors(ws)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_round_backward(name, dtype):
+    """The backward in rounds on the same shapes: every gradient against the oracle's
+    reverse pass, the table restored bit for bit, and stages of 64 tokens giving the
+    same bits as one stage."""
+    S, T, N, W, R, dv = SHAPES[name]
+    rng = np.random.default_rng(2000 + len(name) * 7 + W + R)
+    lists = lambda k: np.stack([np.stack([np.sort(rng.choice(N, k, replace=False)) for _ in range(T)])
+                                for _ in range(S)]).astype(np.int32)
+    wi, ri = lists(W), lists(R)
+    wv = (rng.random((S, T, W)) * 2 / np.sqrt(W)).astype(np.float32)
+    rv = rng.random((S, T, R)).astype(np.float32)
+    dev = lambda a, dt=None: torch.from_numpy(np.ascontiguousarray(a))[:, None].to(DEV, dt)
+    v, al, be = (dev(x.astype(np.float32), dtype) for x in (rng.standard_normal((S, T, dv)), rng.uniform(0.1, 1, (S, T)),
+                                                            rng.uniform(0.1, 1, (S, T))))
+    m0, dy = rng.standard_normal((S, N, dv)).astype(np.float32), rng.standard_normal((S, T, dv)).astype(np.float32)
+    dmT = rng.standard_normal((S, N, dv)).astype(np.float32)
+    f64 = lambda t: t[:, 0].double().cpu().numpy()
+    memo = m0.astype(np.float64)
+    _, so = oracle.scan_fwd(wi, wv, ri, rv, f64(v), f64(al), f64(be), memo, save=True)
+    go = oracle.scan_bwd(wi, wv, ri, rv, f64(v), f64(al), f64(be), memo, so, dy.astype(np.float64),
+                         dmem_T=dmT.astype(np.float64))
+    args = (dev(wi), dev(wv), dev(ri), dev(rv), v, al, be)
+    mem, saved = dev(m0), sdm.saved_buffer(S, 1, T, W, dv, DEV)
+    sdm.scan_fwd(*args, mem, saved=saved)
+    mem_T = mem.clone()
+    got = []
+    for chunk in (T, 64):
+        mem.copy_(mem_T)
+        got.append(sdm.scan_bwd(*args, mem, saved, dev(dy), dmem_T=dev(dmT), want_dqk=False, chunk=chunk))
+        torch.cuda.synchronize()
+        assert torch.equal(mem, dev(m0))
+    for k in ("dv", "dalpha", "dbeta", "dmem0", "dw_val", "dr_val"):
+        assert torch.equal(got[0][k], got[1][k]), k
+        assert rel_err(f64(got[0][k]), np.asarray(go[k]).reshape(f64(got[0][k]).shape)) <= REGRESSION_TOL, k
