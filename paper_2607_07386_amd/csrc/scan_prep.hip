@@ -17,6 +17,8 @@
 // visits all of a chain and keeps the nearest entry: the result does not depend
 // on the order.  The lists need not be sorted.  The same walk finds the token's
 // own entry of the slot.
+#include <algorithm>
+
 #include "sdm_common.h"
 #include "sdm_internal.h"
 
@@ -24,9 +26,15 @@ namespace {
 
 constexpr int THREADS = 256;
 
-// Tokens per workgroup: fewer for longer lists, so that the table and the lists
-// stay near 20 KB of LDS (the records are also built beside a running scan).
-int prep_tokens(int nrow) { return nrow <= 96 ? 32 : 16; }
+// Tokens per workgroup, a multiple of the round `per`.  A window of a few tokens
+// (reach) costs small workgroups little, and the records of those scans are built
+// beside a scan that fills the device: 8 tokens (6 KB of LDS at 32 rows) there take
+// the least from it (1.4B-shaped forward with 64, 32, 16, 8 tokens: 6.13, 6.08,
+// 6.02, 5.94 ms; training step 11.81, 11.74, 11.70, 11.57).  Deep windows, whose
+// lists every workgroup enters again, take 32, or 16 with long lists.
+int prep_tokens(int nrow, int reach, int per) {
+    return std::max(per, reach <= 8 ? 8 : nrow <= 96 ? 32 : 16);
+}
 
 // Hash table size (log2) for n entries: between 2/3 and 4/3 heads per entry.
 int hash_bits(int n) {
@@ -304,7 +312,7 @@ __global__ __launch_bounds__(THREADS) void bwd_prep_kernel(
 // round and keeps `depth` rounds in flight.
 hipError_t sdm_launch_fwd_prep(const ScanFwdArgs& a, int per_log2, int depth, hipStream_t st) {
     const int S = a.B * a.H, per = 1 << per_log2;
-    const int pt = prep_tokens(a.W + a.R);
+    const int pt = prep_tokens(a.W + a.R, depth * per, per);
     const int lists = pt + depth * per;
     const int bits = hash_bits(lists * a.W);
     dim3 grid((a.te - a.tb + pt - 1) / pt, S);
@@ -323,7 +331,7 @@ hipError_t sdm_launch_fwd_prep(const ScanFwdArgs& a, int per_log2, int depth, hi
 // tokens a round, counted from te down, and keeps `depth` rounds in flight.
 hipError_t sdm_launch_bwd_prep(const ScanBwdArgs& a, int per_log2, int depth, hipStream_t st) {
     const int S = a.B * a.H;
-    const int pt = prep_tokens(a.W + a.R);
+    const int pt = prep_tokens(a.W + a.R, depth << per_log2, 1 << per_log2);
     const int n = (pt + ((depth + 1) << per_log2) - 1) * (a.W + a.R);
     const int bits = hash_bits(n);
     dim3 grid((a.te - a.tb + pt - 1) / pt, S);
