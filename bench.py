@@ -507,7 +507,7 @@ def main():
                 ("sequential", lambda: sdm.scan_fwd(wi, wv, ri, rv, v, al, be, mem, workspace=wsf, y=yl),
                  ("fwd_prep", "fwd_scan")),
                 ("chunked", lambda: sdm.scan_fwd_chunked(wi, wv, ri, rv, v, al, be, mem, workspace=wsc, y=yl),
-                 ("chunk_coef", "chunk_scan"))):
+                 ("fwd_prep", "fwd_scan", "chunk_coef", "chunk_scan"))):
             log(f"long context: timing the {name} scan")
             fn()
             torch.cuda.synchronize()
