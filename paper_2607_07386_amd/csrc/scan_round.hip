@@ -271,7 +271,9 @@ __global__ __launch_bounds__(NWV * SDM_WAVE) void scan_fwd_round_kernel(
         }
         // the helpers' pace (device scope, so that it leaves the compute unit; no helpers: out of bounds)
         __builtin_amdgcn_raw_buffer_store_b32(r, prs, w == 0 && lane == 0 ? 0 : (int)OOB, 0, 16);
-        const uint32_t lc = tok ? c.lc4 : OOB;   // slot offsets are below 2 GiB: OOB + offset stays out
+        // For the rows: a slot's offset is below 2 GiB, so OOB + offset stays out.  Not for y: a token past
+        // the end may lie at 2 GiB and more, where the sum would wrap to one of y's first rows.
+        const uint32_t lc = tok ? c.lc4 : OOB;
         v4f up = v4zero(), yp = v4zero();
         v4f Dk[K];
         __amdgpu_buffer_rsrc_t srs;   // the token's saved rows
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(NWV * SDM_WAVE) void scan_fwd_round_kernel(
         __hip_atomic_store(&prog[w], r + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
         __builtin_amdgcn_raw_buffer_store_b128(
             __builtin_bit_cast(u32x4, v4fma(yc, e, yp)), yrs,
-            (int)(c.rg == 0 && c.colok ? __umul24((uint32_t)t, c.dv4) + lc : OOB), 0, 0);
+            (int)(tok && c.rg == 0 && c.colok ? (uint32_t)t * c.dv4 + c.lc4 : OOB), 0, 0);
         // the record of round r + D + 1 to LDS (loaded a round ago), the next into
         // registers, then the rows of round r + D
         const int after = nxt + 1 == Geo::NREC ? 0 : nxt + 1;
@@ -367,9 +369,9 @@ bool round_plan(const ScanFwdArgs& a, RoundPlan* p) {
     // a forced geometry is one of scan_fwd.hip's
     if (!sdm_line_io_enabled() || sdm_scan_slice_width() || sdm_scan_prefetch()) return false;
     if (a.dv < CW) return false;
-    // the table rows' and y's 32-bit offsets (and the 24-bit multiplies: N, T < 2^24)
+    // the table rows' and y's 32-bit offsets (and the slots' 24-bit multiply)
     if ((size_t)a.N * a.dv * 4 >= ((size_t)1 << 31) || a.N >= (1 << 24)) return false;
-    if ((size_t)a.T * a.dv * 4 >= ((size_t)1 << 31) || a.T >= (1 << 24)) return false;
+    if ((size_t)a.T * a.dv * 4 >= ((size_t)1 << 31)) return false;
     const int m = std::max(a.W, a.R);
     if (m > RG * 8) return false;
     if (a.W == a.R && (m == 32 || m == 64) && a.dv % 32 == 0) {

@@ -82,6 +82,25 @@ def test_round_scan_stages_and_helpers():
         assert torch.equal(y, out[0][0]) and torch.equal(mem, out[0][1])
 
 
+def test_round_scan_two_gib_of_output():
+    """A stream whose y ends just below 2 GiB, at a length that leaves waves of the last
+    rounds without a token: those tokens' offsets lie past 2 GiB, and what is stored
+    for them must not land in y's first rows."""
+    T, N, k, dv, head = 559239, 64, 8, 960, 64
+    assert T * dv * 4 < 2 ** 31 <= (T + 8) * dv * 4
+    g = torch.Generator(device=DEV).manual_seed(3)
+    lists = lambda: (torch.randint(0, N // k, (1, 1, T, k), generator=g, device=DEV) +
+                     torch.arange(k, device=DEV) * (N // k)).int()
+    u = lambda *sh: torch.rand(sh, generator=g, device=DEV)
+    args = [lists(), u(1, 1, T, k) / k, lists(), u(1, 1, T, k),
+            torch.randn((1, 1, T, dv), generator=g, device=DEV, dtype=torch.bfloat16), u(1, 1, T).bfloat16(),
+            u(1, 1, T).bfloat16()]
+    y = sdm.scan_fwd(*args, torch.zeros((1, 1, N, dv), device=DEV))[:, :, :head].clone()
+    short = sdm.scan_fwd(*(a[:, :, :head].contiguous() for a in args), torch.zeros((1, 1, N, dv), device=DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(y, short)
+
+
 @pytest.mark.parametrize("T", [130, 2100])
 def test_chunked_call_in_rounds(T):
     """sdm_scan_fwd_chunked on a table large enough for the scan in rounds (one range,
