@@ -38,11 +38,12 @@ __global__ __launch_bounds__(256) void gates_kernel(const VT* __restrict__ a, co
 
 // One workgroup per head: every (b, t) of the head, in a fixed order per
 // thread, then a fixed tree over the threads.  Bound by the few workgroups'
-// exponentials and logarithms: 16 waves a head, and no division (64 streams of
-// 4096 tokens, 16 heads, with the forward gates: 100 us by 4 waves dividing a
-// flat index by T per element, 47 now).  dz = dalpha * (-A alpha
-// sigma(z)), da = dz, db = dbeta beta (1 - beta); dA and db_dt are the head's
-// sums of dalpha * (-softplus(z) alpha) and of dz.
+// exponentials and logarithms: 16 waves a head over the head's tokens of all
+// sequences, stepping (b, t) by a fixed stride with a carry (16 heads, 4
+// sequences of 4096 tokens: 65 us by 4 waves dividing a flat index by T per
+// element, 34 now; 512 of 32 tokens: 72, 544 sequence by sequence, 35 now).
+// dz = dalpha * (-A alpha sigma(z)), da = dz, db = dbeta beta (1 - beta); dA and
+// db_dt are the head's sums of dalpha * (-softplus(z) alpha) and of dz.
 constexpr int GB_THREADS = 1024;
 template <typename VT>
 __global__ __launch_bounds__(GB_THREADS) void gates_bwd_kernel(
@@ -54,20 +55,28 @@ __global__ __launch_bounds__(GB_THREADS) void gates_bwd_kernel(
     const int h = blockIdx.x;
     const float Ah = A[h], bh = bdt[h];
     float sA = 0.f, sb = 0.f;
-    for (int bb = 0; bb < B; ++bb) {
-        const size_t base = ((size_t)bb * H + h) * T;
-        for (int t = threadIdx.x; t < T; t += GB_THREADS) {
-            const size_t i = base + t;
-            const float z = ld1(a, i) + bh;
-            const float sp = sdm_softplus(z);
-            const float al = expf(-Ah * sp);
-            const float dal = dalpha[i];
-            const float dz = dal * (-Ah * al * sdm_sigmoid(z));
-            da[i] = dz;
-            sb += dz;
-            sA += dal * (-sp * al);
-            const float be = sdm_sigmoid(ld1(b, i));
-            db[i] = dbeta[i] * be * (1.f - be);
+    const int len = max(T, 1), nb = T > 0 ? B : 0;
+    const int step_b = GB_THREADS / len, step_t = GB_THREADS % len;
+    const size_t step = (size_t)step_b * H * T + step_t, carry = (size_t)(H - 1) * T;
+    int bb = (int)threadIdx.x / len, t = (int)threadIdx.x % len;
+    for (size_t i = ((size_t)bb * H + h) * T + t; bb < nb; i += step) {
+        const float z = ld1(a, i) + bh;
+        const float sp = sdm_softplus(z);
+        const float al = expf(-Ah * sp);
+        const float dal = dalpha[i];
+        const float dz = dal * (-Ah * al * sdm_sigmoid(z));
+        da[i] = dz;
+        sb += dz;
+        sA += dal * (-sp * al);
+        const float be = sdm_sigmoid(ld1(b, i));
+        db[i] = dbeta[i] * be * (1.f - be);
+        bb += step_b;
+        if (t >= T - step_t) {   // into the next sequence's tokens of this head
+            t -= T - step_t;
+            ++bb;
+            i += carry;
+        } else {
+            t += step_t;
         }
     }
     red[0][threadIdx.x] = sA;
@@ -104,8 +113,7 @@ __device__ __forceinline__ float row_sum(float v) {
 }
 
 // A row's pieces of this lane: quad q + j LPR of the row's d_v / 4, j < NQ (zeros
-// past the end).  Rows of up to 8 quads a lane are loaded once and kept in
-// registers; longer ones (NQ = 16) are read again where they are used.
+// past the end), loaded once and kept in registers.
 template <int LPR, int NQ, typename T>
 __device__ __forceinline__ void row_load(v4f (&x)[NQ], const T* p, int dv, int q) {
 #pragma unroll
@@ -168,7 +176,8 @@ __global__ __launch_bounds__(256) void norm_gate_kernel(const float* __restrict_
 // dy = rstd (dn - n mean(dn n)).  dgamma: each workgroup sums do phi(g) n over
 // its rows in a fixed order (per lane across the rows its row group visits,
 // then over row groups and waves through LDS) into part[workgroup][d_v].
-// HBM-bound: y, g and do are read once (kept in registers up to NQ = 8).
+// HBM-bound: y is read once, g and do once up to NQ = 8 and twice in longer rows
+// (their registers would not fit).
 template <typename GT, int LPR, int NQ>
 __global__ __launch_bounds__(256) void norm_gate_bwd_kernel(
     const float* __restrict__ y, const GT* __restrict__ g, const float* __restrict__ gamma, float eps, int act,
