@@ -453,9 +453,11 @@ int sdm_set_scan_prefetch(int pd);
  * (where the per-wave plan takes 8-column slices) or 64, and d_v a multiple of
  * 32.  Each stream's table and saved rows must stay below 2 GiB (32-bit
  * offsets), else the per-wave kernels run.  With all geometry automatic, d_v >=
- * 32 and W, R <= 64, launches of few streams, and all lists that are not 32 or
- * 64 rows on both sides, take scans in rounds of tokens instead (one wave per
- * token on 32 columns).  sdm_set_scan_line_io(0) always
+ * 32 and W, R <= 64, lists of up to 8 rows, and longer ones where few streams or
+ * large tables make it faster, take scans in rounds of tokens instead (one wave
+ * per token on 32 columns).  Whether the forward keeps an undo log enters that
+ * choice: results with and without it agree to rounding, and bit for bit only
+ * where both take the same kernel.  sdm_set_scan_line_io(0) always
  * uses the per-wave kernels
  * (each wave moves its own pieces of the rows), 1 restores the default.  The
  * two do the same arithmetic per slice; results agree to rounding (the sums

@@ -345,21 +345,39 @@ hipError_t launch_bround_k(const ScanBwdArgs& a, const BRoundPlan& p, float* par
 
 }  // namespace
 
-// Which backward launches go in rounds: as the forward's (round_plan in
-// scan_round.hip), with its reasons; the line-cooperative kernel keeps lists of 32
+// Which backward launches go in rounds: as the forward's (round_faster in
+// scan_round.hip), with its reasons.  The line-cooperative kernel keeps lists of 32
 // or 64 rows from half the device's compute units on (128 workgroups of top-32: 2547
-// us by the line kernel, 2138 here; 256: equal within the step's noise) and on
-// tables whose tokens chain.  All other lists (per-wave kernel / here, 128 streams):
-// top-8 3132 / 1927, top-16 5124 / 3608, top-48 13,768 / 10,716.
+// us by the line kernel, 2138 here; 256: equal within the step's noise) and on tables
+// whose tokens chain (256 tokens, 16 streams, top-32: N = 2048 332 / 340 us, 2925 332 /
+// 310; 4 streams, top-64: N = 8192 529 / 567, 11,702 527 / 526, 16,384 529 / 479).  Other
+// lists have the per-wave kernel (2048 tokens, N = 65536, 128 streams: top-8 3132 /
+// 1927, top-16 5124 / 3608, top-48 13,768 / 10,716), which wins on dense tables; here
+// read rows' adjoints link tokens as well, so that the slots that two tokens share go
+// with (W + R)^2 / N.  Its time over this kernel's by that (d_v = 128; limits in
+// brackets):
+//   16 streams   top-16: 8 1.15, 1 1.50; top-24: 8 0.81, 1.4 0.96, 1 1.05 [1]
+//                top-48: 2 0.76, 0.7 0.99, 0.5 1.15 [1/2]
+//   128 streams  top-12: 2 0.72, 0.5 1.10; top-16: 8 0.72, 2 1.00, 1 1.12 [1]
+//                top-24: 8 0.75, 1 1.04; top-40: 1 0.84, 0.7 1.03; top-48: 2 0.92, 1 1.11 [3/4]
+//   512 streams  top-24: 8 0.75, 1 1.03; top-40: 2 0.77, 0.7 1.01, 0.5 1.09; top-48: 1 1.08
+//   rows that end inside a line, 256 streams: d_v = 36 top-24 2 1.23, 1 1.55, top-48 2 1.26,
+//                1.4 1.37; d_v = 68 top-24 2 1.16, top-48 2 1.24 [2, 3/2]; but 512 streams of
+//                d_v = 36, whose second column group is nearly empty, top-48: 1.1 0.77
 bool sdm_bwd_round(const ScanBwdArgs& a) {
     BRoundPlan p;
     if (!sdm_line_io_enabled() || sdm_scan_slice_width() || sdm_scan_prefetch()) return false;
     if (!bround_plan(a, &p)) return false;
-    if (a.W == a.R && (a.W == 32 || a.W == 64) && a.dv % 32 == 0) {
-        if ((int64_t)a.B * a.H * bround_groups(a) > sdm_device_simds() / 8) return false;
-        if ((int64_t)a.W * (a.W + a.R) > a.N) return false;
-    }
-    return true;
+    const int64_t cus = sdm_device_simds() / 4, wgs = (int64_t)a.B * a.H * bround_groups(a);
+    const int64_t pairs = (int64_t)a.W * (a.W + a.R), links = (int64_t)(a.W + a.R) * (a.W + a.R);
+    const int m = std::max(a.W, a.R);
+    if (a.W == a.R && (m == 32 || m == 64) && a.dv % 32 == 0)
+        return wgs <= cus / 2 && 2 * a.N >= (m == 32 ? 3 : 4) * pairs;
+    if (m <= RG) return true;
+    if (m <= RG * 2) return wgs <= cus || a.N >= links;
+    const int ragged = a.dv % CW && wgs > cus && (a.dv > 2 * CW || wgs < 4 * cus) ? 2 : 1;
+    if (m <= RG * 4) return ragged * a.N >= links;
+    return wgs <= cus ? a.N >= 2 * links : 3 * ragged * a.N >= 4 * links;
 }
 int sdm_bwd_round_parts(const ScanBwdArgs& a) { return bround_groups(a); }
 

@@ -354,37 +354,62 @@ bool plan_k(const ScanFwdArgs& a, RoundPlan* p) {
 
 int round_groups(const ScanFwdArgs& a) { return (a.dv + CW - 1) / CW; }
 
-// Which launches take this kernel.  Lists of exactly 32 or 64 rows have the
-// line-cooperative kernel, which moves more bytes per second once every compute
-// unit has work (scan of 2048 tokens, d_v = 128, N = 65536, line kernel against
-// this one in us: top-32 with 16 streams 1112 / 551, 32: 1173 / 820, 64: 1859 /
-// 1515, 128: 2871 / 3219; top-64 with 16 streams 1734 / 1243, 64: 2687 / 3103,
-// 128: 5425 / 6746; 480 workgroups of the 1.4B layer with the undo log 9.5 / 9.3
-// ms, without 4.9 / 4.7, no gain in its steps): so one workgroup per compute unit
-// at most with 32 rows, half of that with 64.  All other lists would take the
-// per-wave kernel, which moves 32-byte pieces of rows: 16 streams top-16 1705 /
-// 410, top-48 2262 / 1535; 128 streams top-8 1972 / 1176, top-16 2079 / 1459,
-// top-48 5655 / 5451.  Rows narrower than a line stay with the per-wave kernel.
+// Whether the kernel can run these arguments, and its geometry for them.
 bool round_plan(const ScanFwdArgs& a, RoundPlan* p) {
-    // a forced geometry is one of scan_fwd.hip's
-    if (!sdm_line_io_enabled() || sdm_scan_slice_width() || sdm_scan_prefetch()) return false;
-    if (a.dv < CW) return false;
+    if (a.dv < CW) return false;   // rows narrower than a line: the per-wave kernel
     // the table rows' and y's 32-bit offsets (and the slots' 24-bit multiply)
     if ((size_t)a.N * a.dv * 4 >= ((size_t)1 << 31) || a.N >= (1 << 24)) return false;
     if ((size_t)a.T * a.dv * 4 >= ((size_t)1 << 31)) return false;
     const int m = std::max(a.W, a.R);
     if (m > RG * 8) return false;
-    if (a.W == a.R && (m == 32 || m == 64) && a.dv % 32 == 0) {
-        const int64_t cus = sdm_device_simds() / 4;
-        if ((int64_t)a.B * a.H * round_groups(a) > (m == 32 && !a.saved ? cus : cus / 2)) return false;
-        // tables so small that most tokens of a round share slots: the round is then a
-        // chain of its tokens (top-32 of 1024 slots: 0.56 us a token against 0.53)
-        if ((int64_t)a.W * (a.W + a.R) > a.N) return false;
-    }
     if (m <= RG) return plan_k<1>(a, p);
     if (m <= RG * 2) return plan_k<2>(a, p);
     if (m <= RG * 4) return plan_k<4>(a, p);
     return plan_k<8>(a, p);
+}
+
+// a forced geometry is one of scan_fwd.hip's or scan_chunk.hip's
+bool geometry_forced() { return !sdm_line_io_enabled() || sdm_scan_slice_width() || sdm_scan_prefetch(); }
+
+// lists that the line-cooperative kernel takes
+bool line_lists(const ScanFwdArgs& a) { return a.W == a.R && (a.W == 32 || a.W == 64) && a.dv % 32 == 0; }
+
+// Whether it is the faster kernel for them.  Two things speak against it.
+//  * Lists of exactly 32 or 64 rows have the line-cooperative kernel, which moves
+//    more bytes per second once every compute unit has work (scan of 2048 tokens,
+//    d_v = 128, N = 65536, line kernel against this one in us: top-32 with 16 streams
+//    1112 / 551, 32: 1173 / 820, 64: 1859 / 1515, 128: 2871 / 3219; top-64 with 16
+//    streams 1734 / 1243, 64: 2687 / 3103, 128: 5425 / 6746; 480 workgroups of the 1.4B
+//    layer with the undo log 9.5 / 9.3 ms, without 4.9 / 4.7, no gain in its steps): so
+//    one workgroup per compute unit at most with 32 rows, half of that with 64.
+//  * Where tokens of a round share slots they wait for each other.  A token's rows
+//    meet about (tokens of a round) W (W + R) / N slots that another writes, and the
+//    limits are where that costs what the rounds gain (256 tokens of top-32, 16
+//    streams, against the line kernel: N = 2048 155 / 170 us, 2925 153 / 153, 4096 152 /
+//    144; top-64: 8192 223 / 253, 11,702 220 / 234, 16,384 219 / 210).
+// Other lists would take the per-wave kernel, which moves 32-byte pieces of rows: it
+// loses on large tables (16 streams of 2048 tokens top-16 1705 / 410 us, 128 streams
+// top-8 1972 / 1176) and at up to 16 rows nearly everywhere.  On dense tables it wins
+// with longer lists, and earlier where two workgroups share a compute unit; the undo
+// log's stores cost it more.  Its time over this kernel's (d_v = 128, by W (W + R) / N;
+// limits in brackets, without / with the log):
+//   16 streams   top-24: 4 0.87, 1.4 1.00, 1 1.08, 0.25 1.49 [4/3]
+//                top-48: 4 0.75, 0.7 1.00, 0.5 1.06, 0.25 1.18 [3/5]
+//   128 streams  top-16: 4 1.21 / 1.21; top-24: 2 0.73 / 0.76, 0.7 0.87 / 1.11, 0.5 0.95 /
+//                1.12; top-48: 2 0.62 / 1.10, 0.5 0.94 / 1.15, 0.25 1.01 / 1.24 [1/2, 5/4]
+//   512 streams  top-16: 4 0.80 / 1.37, 2 0.87 / 1.52, 1.4 1.03 [3/2, 15/4]; top-24: 4 0.45 /
+//                0.88, 2 0.61 / 1.11, 0.5 1.05 / 1.29; top-48: 1 0.95 / 1.17, 0.5 1.11
+//   rows that end inside a line, top-48: 256 streams of d_v = 36 2 0.94 / 1.39, 1 1.10, 0.7
+//                1.38; of d_v = 68 2 0.92 / 1.37, 1 1.32 [1, 5/2]
+bool round_faster(const ScanFwdArgs& a) {
+    const int64_t cus = sdm_device_simds() / 4, wgs = (int64_t)a.B * a.H * round_groups(a);
+    const int64_t pairs = (int64_t)a.W * (a.W + a.R);
+    const int m = std::max(a.W, a.R);
+    if (line_lists(a)) return wgs <= (m == 32 && !a.saved ? cus : cus / 2) && 2 * a.N >= 3 * pairs;
+    if (m <= RG) return true;
+    if (wgs <= cus) return m <= RG * 2 || (m <= RG * 4 ? 4 * a.N >= 3 * pairs : 3 * a.N >= 5 * pairs);
+    const int64_t limit = (a.saved ? 5 : 2) * (m > RG * 4 && a.dv % CW ? 2 : 1);   // quarters, of pairs / N
+    return m <= RG * 2 ? wgs <= 2 * cus || 3 * limit * a.N >= 4 * pairs : limit * a.N >= 4 * pairs;
 }
 
 // Helpers per main workgroup: as many as free compute units allow, at most two
@@ -430,7 +455,8 @@ hipError_t launch_round_k(const ScanFwdArgs& a, const RoundPlan& p, hipStream_t 
 
 bool sdm_round_scan(const ScanFwdArgs& a, int* per_log2, int* depth, int* lds) {
     RoundPlan p;
-    if (!round_plan(a, &p)) return false;
+    if (a.rounds == 0 || !round_plan(a, &p)) return false;
+    if (a.rounds < 0 && (geometry_forced() || !round_faster(a))) return false;
     *per_log2 = __builtin_ctz((unsigned)p.nwv);
     *depth = p.depth;
     *lds = p.lds;

@@ -114,6 +114,7 @@ struct ScanFwdArgs {
     // and those below 1e-30, are taken as 1e-30, and gates <= 0 flagged (bit 1 of
     // the error word) when the records are made.
     bool positive_gates = false;
+    int rounds = -1;   // the scan in rounds of tokens: 1 yes, 0 no, or -1 to decide from the shape
 };
 hipError_t sdm_launch_scan_fwd(const ScanFwdArgs& a, hipStream_t st);   // prep + scan
 size_t sdm_fwd_scan_lds(const ScanFwdArgs& a);   // LDS of one workgroup of that scan

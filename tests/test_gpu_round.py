@@ -1,9 +1,9 @@
 """The forward scan in rounds of tokens against the oracle: list lengths at the
 edges of its rows-per-lane steps, row widths that leave lanes of the last column
-group without columns, sequences that end inside a round, tables small enough
-that most tokens share slots (waits inside a round, ring rows of earlier
-rounds) and large enough that few do, with and without the undo log; and with
-helper workgroups, which must not change a bit."""
+group without columns, sequences that end inside a round, lists from so few slots that most tokens
+share some (waits inside a round, ring rows of earlier rounds) and from so many
+that few do, with and without the undo log; with helper workgroups, which must
+not change a bit; and which shapes take it."""
 import numpy as np
 import pytest
 import torch
@@ -14,31 +14,45 @@ from tests.gpu_util import DEV, REGRESSION_TOL, rel_err
 
 pytestmark = pytest.mark.gpu
 
-# (streams, T, N, W, R, d_v)
+# (streams, T, N, W, R, d_v, slots in use): tables of N slots that the dispatch gives to
+# this kernel, and lists drawn from fewer of them (evenly spread), so that tokens chain
 SHAPES = {
-    "one-row": (3, 37, 5, 1, 1, 32),
-    "k1-full": (2, 200, 40, 8, 8, 64),
-    "k1-odd": (3, 41, 30, 7, 3, 36),
-    "k2": (2, 65, 64, 16, 16, 32),
-    "k2-odd": (2, 50, 64, 9, 15, 100),
-    "k4-dense": (2, 150, 40, 32, 32, 64),
-    "k4-sparse": (16, 160, 4096, 32, 32, 32),
-    "k4-mixed": (3, 77, 200, 32, 17, 128),
-    "k8-dense": (2, 130, 80, 64, 64, 32),
-    "k8-sparse": (8, 131, 9000, 64, 64, 64),
-    "k8-mixed": (3, 53, 300, 48, 24, 100),
-    "k8-edge": (2, 4, 99, 33, 64, 44),
+    "one-row": (3, 37, 5, 1, 1, 32, 5),
+    "k1-full": (2, 200, 40, 8, 8, 64, 40),
+    "k1-odd": (3, 41, 30, 7, 3, 36, 30),
+    "k2": (2, 65, 64, 16, 16, 32, 64),
+    "k2-odd": (2, 50, 64, 9, 15, 100, 64),
+    "k4-dense": (2, 150, 3072, 32, 32, 64, 40),
+    "k4-sparse": (16, 160, 4096, 32, 32, 32, 4096),
+    "k4-mixed": (3, 77, 2401, 32, 17, 128, 200),
+    "k8-dense": (2, 130, 16384, 64, 64, 32, 80),
+    "k8-sparse": (8, 131, 16384, 64, 64, 64, 9000),
+    "k8-mixed": (3, 53, 10368, 48, 24, 100, 300),
+    "k8-edge": (2, 4, 18818, 33, 64, 44, 99),
 }
+
+
+def _lists(rng, S, T, N, k, use):
+    ids = np.sort(rng.choice(N, use, replace=False))
+    return np.stack([np.stack([ids[np.sort(rng.choice(use, k, replace=False))] for _ in range(T)])
+                     for _ in range(S)]).astype(np.int32)
+
+
+def _other_kernel(fn):
+    """fn() by the kernels of a forced geometry, which never go in rounds."""
+    sdm.set_scan_prefetch(4)
+    try:
+        return fn()
+    finally:
+        sdm.set_scan_prefetch(0)
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("name", list(SHAPES))
 def test_round_scan(name, dtype):
-    S, T, N, W, R, dv = SHAPES[name]
+    S, T, N, W, R, dv, use = SHAPES[name]
     rng = np.random.default_rng(1000 + len(name) * 7 + W + R)
-    lists = lambda k: np.stack([np.stack([np.sort(rng.choice(N, k, replace=False)) for _ in range(T)])
-                                for _ in range(S)]).astype(np.int32)
-    wi, ri = lists(W), lists(R)
+    wi, ri = _lists(rng, S, T, N, W, use), _lists(rng, S, T, N, R, use)
     wv = (rng.random((S, T, W)) * 2 / np.sqrt(W)).astype(np.float32)
     rv = rng.random((S, T, R)).astype(np.float32)
     dev = lambda a, dt=None: torch.from_numpy(np.ascontiguousarray(a))[:, None].to(DEV, dt)
@@ -61,6 +75,9 @@ def test_round_scan(name, dtype):
         assert rel_err(f64(got), np.asarray(ref).reshape(f64(got).shape)) <= REGRESSION_TOL
     y2, mem2, _ = run(False)
     assert torch.equal(y, y2) and torch.equal(mem, mem2)
+    # the sums over rows are in another order there: the same bits would mean the same kernel
+    if W > 1:
+        assert not torch.equal(y, _other_kernel(lambda: run(False))[0])
 
 
 def test_round_scan_stages_and_helpers():
@@ -141,11 +158,9 @@ def test_round_backward(name, dtype):
     """The backward in rounds on the same shapes: every gradient against the oracle's
     reverse pass, the table restored bit for bit, and stages of 64 tokens giving the
     same bits as one stage."""
-    S, T, N, W, R, dv = SHAPES[name]
+    S, T, N, W, R, dv, use = SHAPES[name]
     rng = np.random.default_rng(2000 + len(name) * 7 + W + R)
-    lists = lambda k: np.stack([np.stack([np.sort(rng.choice(N, k, replace=False)) for _ in range(T)])
-                                for _ in range(S)]).astype(np.int32)
-    wi, ri = lists(W), lists(R)
+    wi, ri = _lists(rng, S, T, N, W, use), _lists(rng, S, T, N, R, use)
     wv = (rng.random((S, T, W)) * 2 / np.sqrt(W)).astype(np.float32)
     rv = rng.random((S, T, R)).astype(np.float32)
     dev = lambda a, dt=None: torch.from_numpy(np.ascontiguousarray(a))[:, None].to(DEV, dt)
@@ -168,6 +183,52 @@ def test_round_backward(name, dtype):
         got.append(sdm.scan_bwd(*args, mem, saved, dev(dy), dmem_T=dev(dmT), want_dqk=False, chunk=chunk))
         torch.cuda.synchronize()
         assert torch.equal(mem, dev(m0))
+    mem.copy_(mem_T)
+    other = _other_kernel(lambda: sdm.scan_bwd(*args, mem, saved, dev(dy), dmem_T=dev(dmT), want_dqk=False))
+    assert not all(torch.equal(got[0][k], other[k]) for k in other if other[k] is not None)
     for k in ("dv", "dalpha", "dbeta", "dmem0", "dw_val", "dr_val"):
         assert torch.equal(got[0][k], got[1][k]), k
         assert rel_err(f64(got[0][k]), np.asarray(go[k]).reshape(f64(got[0][k]).shape)) <= REGRESSION_TOL, k
+
+
+@pytest.mark.parametrize("S,N,k,plain,log,bwd,dv", [(130, 4607, 48, 0, 1, 0, 36), (130, 4608, 48, 1, 1, 0, 36), (130, 6144, 48, 1, 1, 1, 36),
+                                                     (512, 6144, 48, 1, 1, 0, 36)] + [t + (32,) for t in [
+    # workgroups: 4 below one per compute unit, 260 above one, 520 above two
+    (4, 16, 8, 1, 1, 1), (520, 16, 8, 1, 1, 1),                                  # up to 8 rows: any table
+    (4, 32, 16, 1, 1, 1), (260, 32, 16, 1, 1, 0), (520, 136, 16, 0, 0, 0),       # up to 16: but dense ones by many streams
+    (520, 341, 16, 0, 1, 0), (520, 342, 16, 1, 1, 0), (520, 1024, 16, 1, 1, 1),
+    (4, 863, 24, 0, 0, 0), (4, 864, 24, 1, 1, 0), (4, 2304, 24, 1, 1, 1),
+    (260, 921, 24, 0, 0, 0), (260, 2303, 24, 0, 1, 0), (260, 2304, 24, 1, 1, 1),
+    (4, 7679, 48, 0, 0, 0), (4, 7680, 48, 1, 1, 0), (4, 18432, 48, 1, 1, 1),
+    (260, 9215, 48, 0, 1, 0), (260, 9216, 48, 1, 1, 0), (260, 12288, 48, 1, 1, 1),
+    (4, 3071, 32, 0, 0, 0), (4, 3072, 32, 1, 1, 1),                              # the line kernel's lists
+    (4, 12287, 64, 0, 0, 0), (4, 12288, 64, 1, 1, 0), (4, 16384, 64, 1, 1, 1)]])
+def test_which_scans_go_in_rounds(S, N, k, plain, log, bwd, dv):
+    """Tables on which the tokens of a round wait for each other keep the other scan
+    kernels, without and with the undo log and in the backward: their bits are a forced
+    geometry's there, and only there (the sums over rows are in another order).  A
+    workgroup per stream with d_v = 32, two with 36."""
+    T = 32
+    g = torch.Generator(device=DEV).manual_seed(S + N + k)
+    u = lambda *sh: torch.rand(sh, generator=g, device=DEV)
+    lists = lambda: (torch.randint(0, N // k, (1, S, T, k), generator=g, device=DEV) +
+                     torch.arange(k, device=DEV) * (N // k)).int()
+    args = (lists(), u(1, S, T, k) / k, lists(), u(1, S, T, k), u(1, S, T, dv) - 0.5, u(1, S, T), u(1, S, T))
+    dy = u(1, S, T, dv) - 0.5
+
+    def scans():
+        y = sdm.scan_fwd(*args, torch.zeros((1, S, N, dv), device=DEV))
+        mem, saved = torch.zeros((1, S, N, dv), device=DEV), sdm.saved_buffer(1, S, T, k, dv, DEV)
+        y_log = sdm.scan_fwd(*args, mem, saved=saved)
+        # the backward from one state, whichever kernel ran before
+        mem.zero_()
+        sdm.set_scan_line_io(False)
+        try:
+            sdm.scan_fwd(*args, mem, saved=saved)
+        finally:
+            sdm.set_scan_line_io(True)
+        gr = sdm.scan_bwd(*args, mem, saved, dy, want_dqk=False)
+        return y, y_log, torch.cat([gr[n].flatten() for n in ("dv", "dalpha", "dw_val", "dr_val")])
+
+    same = [torch.equal(a, b) for a, b in zip(scans(), _other_kernel(scans))]
+    assert same == [not plain, not log, not bwd]
