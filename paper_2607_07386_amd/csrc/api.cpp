@@ -456,18 +456,11 @@ int sdm_scan_fwd_chunked(const int32_t* w_idx, const float* w_val, int W, const 
         b.te = std::min(T, bound(r + 1) * SDM_CHUNK);
         return b;
     };
-    // Unless a width is forced, shapes that the scan in rounds of tokens takes run
-    // it, on records instead of coefficients: 16 streams of 65,536 tokens (N =
-    // 262,144, top-32) 16.0 ms against 22.6, of 4096 tokens 1.36 against 1.81, top-64
-    // 2.83 against 5.31, top-8 0.73 against 0.94.  Its tokens wait for each other
-    // where they share slots, the chunk form's do not: with W <= 32 (the narrow
-    // kernel) tables below about 10 W (W + R) slots stay with the chunk form (top-32:
-    // N = 8100 1.57 against 1.44 ms, 12,100 1.42 / 1.47, 16,384 1.37 / 1.48; top-16:
-    // N = 4096 1.04 / 0.98, 8100 0.94 / 0.99).
+    // Unless a geometry is forced, shapes that the scan in rounds of tokens does faster
+    // run it, on records instead of coefficients.
     a.positive_gates = true;
-    int per_log2, depth, lds;
-    const bool rounds = sdm_chunk_cols() == 0 && (W > 32 || N >= (int64_t)10 * W * (W + R)) &&
-                        sdm_round_scan(a, &per_log2, &depth, &lds);
+    const bool rounds = sdm_chunk_cols() == 0 && sdm_round_beats_chunk(a, sdm_chunk_cols_for(a) == 8);
+    a.rounds = rounds ? 1 : 0;   // one decision for every range, records and scan
     auto coef = [&](const ScanFwdArgs& b, hipStream_t s) {
         if (rounds) return sdm_launch_fwd_prep_range(b, s);
         SdmProfScope ps(SDM_K_CHUNK_COEF, s);

@@ -960,6 +960,8 @@ hipError_t launch_chunk_narrow(const ScanFwdArgs& a, hipStream_t st) {
     return rows16 ? launch_chunk_narrow_t<VT, 16, 16, false>(a, st) : launch_chunk_narrow_t<VT, 32, 16, false>(a, st);
 }
 
+}  // namespace
+
 // Workgroup width.  sdm_set_chunk_scan_cols forces 8 (the narrow kernel, d_v a
 // multiple of 8), 16 or 32 columns.  Otherwise the narrow kernel runs when its
 // workgroups fit the chip at one per CU and it keeps the gathered write rows in
@@ -970,7 +972,7 @@ hipError_t launch_chunk_narrow(const ScanFwdArgs& a, hipStream_t st) {
 // narrow workgroups, two rounds): 6.8 against 5.4 ms.  The narrow workgroups
 // hold 117 KB of LDS, so the next range's coefficient workgroups do not run
 // beside them.  16-column workgroups of the wide kernel: 41.0 against 35.2 ms.
-int chunk_cols_for(const ScanFwdArgs& a) {
+int sdm_chunk_cols_for(const ScanFwdArgs& a) {
     const int forced = sdm_chunk_cols();
     if (forced == 8 && a.dv % NCOL == 0) return 8;
     if (forced == 16 || forced == 32) return forced;
@@ -979,9 +981,10 @@ int chunk_cols_for(const ScanFwdArgs& a) {
     return 32;
 }
 
+namespace {
 template <typename VT>
 hipError_t launch_chunk_scan(const ScanFwdArgs& a, hipStream_t st) {
-    switch (chunk_cols_for(a)) {
+    switch (sdm_chunk_cols_for(a)) {
         case 8: return launch_chunk_narrow<VT>(a, st);
         case 16: return launch_chunk_scan_cols<VT, 16>(a, st);
         default: return launch_chunk_scan_cols<VT, 32>(a, st);

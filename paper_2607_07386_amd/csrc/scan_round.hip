@@ -463,6 +463,37 @@ bool sdm_round_scan(const ScanFwdArgs& a, int* per_log2, int* depth, int* lds) {
     return true;
 }
 
+// Whether the scan in rounds of tokens is faster than the chunk form (`narrow`: its
+// 8-column workgroups).  Its tokens wait for each other where they share slots, the
+// chunk form's do not, so that it takes larger tables; the chunk form's workgroups of
+// 32 columns move more bytes than they need, so that it loses with many streams.
+// Calls of 2048 tokens, d_v = 128, chunk form / rounds in us at slots N:
+//   top-32, 16 streams 8192 737 / 715, 16,384 730 / 573, 262,144 854 / 515; 8: 16,384 560 /
+//     570, 32,768 547 / 474; 32 (wide): 16,384 1189 / 759.  top-16, 8 streams: 4096 371 /
+//     416, 8192 398 / 346.  Write 8, read 32, 8 streams: 4096 325 / 579, 16,384 387 /
+//     442, 32,768 396 / 399: with narrow workgroups the longer list counts.
+//   Over 32 rows a round is a chain of long tokens: top-40, 8 streams 1024 1035 / 2701,
+//     32,768 1105 / 1312, 65,536 1213 / 1170; 16: 16,384 1152 / 1524, 32,768 1314 / 1335;
+//     32: 16,384 1484 / 1557; 64: 4096 2043 / 2224, 8192 2304 / 1912; 128: 4096 4065 / 3184.
+//     From 49 write rows on the chunk form holds fewer workgroups: top-56, 16 streams 8192
+//     1978 / 2119, 16,384 2011 / 1782; 64: 4096 2929 / 2590.  Narrow, write 8, read 64: 8
+//     streams 32,768 886 / 1000, 65,536 1005 / 942; 16: 16,384 1041 / 1113, 32,768 1190 / 1017.
+//   Lists of exactly 64 rows (whole lines, no bounds checks): 16 streams 8192 2194 / 1825.
+bool sdm_round_beats_chunk(const ScanFwdArgs& a, bool narrow) {
+    RoundPlan p;
+    if (geometry_forced() || !round_plan(a, &p)) return false;
+    const int64_t cus = sdm_device_simds() / 4, wgs = (int64_t)a.B * a.H * round_groups(a);
+    const int64_t pairs = (int64_t)a.W * (a.W + a.R);
+    const int m = std::max(a.W, a.R), rows = m <= RG ? RG : m <= RG * 2 ? RG * 2 : RG * 4;
+    if (line_lists(a) && wgs > (m == 32 ? cus : cus / 2)) return false;
+    if (line_lists(a) && m == 64) return a.N >= pairs;
+    if (a.W <= 32 && a.N < 10 * pairs) return false;
+    if (m <= 32) return !narrow || a.N >= 20 * rows * rows;
+    if (narrow) return a.N >= 32768;
+    if (a.W > 48) return a.N >= std::max<int64_t>(4096, std::min<int64_t>(16384, (1 << 20) / wgs));
+    return a.N >= std::max<int64_t>(4096, std::min<int64_t>(65536, (1 << 21) / wgs));
+}
+
 hipError_t sdm_launch_round_scan(const ScanFwdArgs& a, hipStream_t st) {
     RoundPlan p;
     if (!round_plan(a, &p)) return hipErrorInvalidConfiguration;

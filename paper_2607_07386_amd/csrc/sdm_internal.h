@@ -124,6 +124,7 @@ hipError_t sdm_launch_fwd_scan_range(const ScanFwdArgs& a, hipStream_t st);
 // The scan in rounds of tokens (scan_round.hip): whether these arguments take it,
 // with the prep kernel's window and a workgroup's LDS; and its launch.
 bool sdm_round_scan(const ScanFwdArgs& a, int* per_log2, int* depth, int* lds);
+bool sdm_round_beats_chunk(const ScanFwdArgs& a, bool narrow);
 hipError_t sdm_launch_round_scan(const ScanFwdArgs& a, hipStream_t st);
 // SIMDs (4 per compute unit) of the current device; 1024 if it cannot be queried.
 int sdm_device_simds();
@@ -154,6 +155,7 @@ hipError_t sdm_launch_fwd_prep(const ScanFwdArgs& a, int per_log2, int depth, hi
 bool sdm_chunk_shape_ok(int W, int R);
 // Forced columns per workgroup of the chunked scan (16 or 32), or 0 for automatic.
 int sdm_chunk_cols();
+int sdm_chunk_cols_for(const ScanFwdArgs& a);   // the columns that these arguments run
 size_t sdm_chunk_ws_bytes(int B, int H, int T, int W, int R);
 hipError_t sdm_launch_chunk_coef(const ScanFwdArgs& a, hipStream_t st);
 hipError_t sdm_launch_chunk_scan(const ScanFwdArgs& a, hipStream_t st);

@@ -152,6 +152,34 @@ def test_chunked_call_in_rounds(T):
             sdm.check_device_errors(ws)
 
 
+@pytest.mark.parametrize("S,N,W,R,dv,rounds", [
+    (16, 1279, 8, 8, 128, 0), (16, 1280, 8, 8, 128, 1), (16, 20479, 32, 32, 128, 0), (16, 20480, 32, 32, 128, 1),
+    (8, 3200, 8, 32, 128, 0), (8, 20480, 8, 32, 128, 1), (32, 3200, 8, 32, 128, 1),     # narrow or wide chunk kernel
+    (65, 20480, 32, 32, 128, 0),                                                        # the line kernel's from here on
+    (8, 65535, 40, 40, 128, 0), (8, 65536, 40, 40, 128, 1), (32, 16383, 48, 24, 128, 0), (32, 16384, 48, 24, 128, 1),
+    (16, 16383, 56, 56, 128, 0), (16, 16384, 56, 56, 128, 1), (512, 4095, 40, 40, 32, 0), (512, 4096, 40, 40, 32, 1),
+    (8, 32767, 8, 64, 128, 0), (8, 32768, 8, 64, 128, 1), (4, 8191, 64, 64, 128, 0), (4, 8192, 64, 64, 128, 1)])
+def test_which_chunked_calls_go_in_rounds(S, N, W, R, dv, rounds):
+    """The chunk form keeps the tables on which tokens of a round share slots."""
+    T = 64
+    g = torch.Generator(device=DEV).manual_seed(N)
+    u = lambda *sh: torch.rand(sh, generator=g, device=DEV)
+    lists = lambda k: (torch.randint(0, N // k, (1, S, T, k), generator=g, device=DEV) +
+                       torch.arange(k, device=DEV) * (N // k)).int()
+    args = (lists(W), u(1, S, T, W) / W, lists(R), u(1, S, T, R), u(1, S, T, dv), u(1, S, T) / 2 + 0.5, u(1, S, T))
+    mem = torch.zeros((1, S, N, dv), device=DEV)
+    sdm.profile_enable(True)
+    y = sdm.scan_fwd_chunked(*args, mem)
+    torch.cuda.synchronize()
+    ran = sdm.profile_read("fwd_scan")[1], sdm.profile_read("chunk_scan")[1]
+    sdm.profile_enable(False)
+    assert ran == ((1, 0) if rounds else (0, 1))
+    mem2 = torch.zeros_like(mem)
+    y2 = sdm.scan_fwd(*args, mem2)
+    for a, b in ((y, y2), (mem, mem2)):
+        assert ((a - b).abs().max() / b.abs().max()).item() <= REGRESSION_TOL
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("name", list(SHAPES))
 def test_round_backward(name, dtype):
