@@ -755,12 +755,57 @@ __device__ __forceinline__ v4f ld4_any(const bf16_t* p) {
     return v4f{to_f32(p[0]), to_f32(p[1]), to_f32(p[2]), to_f32(p[3])};
 }
 
+// Sub-key scores of tile_scores without matrix cores: plain FMAs, each score one
+// chain over its d_k / 2 terms in order.  A thread takes one sub-key for TG tokens, so
+// the sub-key rows (a line per lane and load) are read once per TG tokens; the
+// tokens' values are the same for the whole wave.  One sub-key and token per thread
+// read a row per score: 206 us a side for 11,655 tokens at sqrt(N) = 100, d_k = 72, 51
+// with eight; 6.4 against 0.25 ms for 16,384 tokens at sqrt(N) = 512, d_k = 200.  For
+// the decode step's single token TG = 1 (16 x 16 streams, sqrt(N) = 256: fp32, d_k = 128
+// 49.6 us a row per score by single words, 29.8 with TG = 8, 22.6 now; bf16, d_k = 72 23.1,
+// 23.6, 17.8).  A choice by nt inside the tile kernels cost their other tiles up to 15%.
+template <typename XT, int E, int HB, int NH, int TG>
+__device__ __forceinline__ void fma_scores(const XT* __restrict__ xs, const XT* __restrict__ cbh, int t0, int nt,
+                                           int dk, int s, float* scores) {
+    constexpr int SP = E * SDM_WAVE;
+    const int dh = dk / 2;
+    for (int i = threadIdx.x; i < (nt + TG - 1) / TG * NH * SP; i += blockDim.x) {
+        const int rest = __builtin_amdgcn_readfirstlane(i / SP), j = i - rest * SP;
+        const int half = HB + rest % NH, tg = rest / NH * TG, n = min(TG, nt - tg);
+        const XT* xr = xs + (size_t)(t0 + tg) * dk + half * dh;
+        const XT* cr = cbh + ((size_t)half * s + min(j, s - 1)) * dh;
+        float acc[TG];
+#pragma unroll
+        for (int u = 0; u < TG; ++u) acc[u] = 0.f;
+        int c = 0;
+        for (; c + 4 <= dh; c += 4) {
+            const v4f b = ld4_any(cr + c);
+#pragma unroll
+            for (int u = 0; u < TG; ++u) {
+                const v4f a = ld4_any(xr + (size_t)min(u, n - 1) * dk + c);
+                acc[u] = fmaf(a.x, b.x, acc[u]);
+                acc[u] = fmaf(a.y, b.y, acc[u]);
+                acc[u] = fmaf(a.z, b.z, acc[u]);
+                acc[u] = fmaf(a.w, b.w, acc[u]);
+            }
+        }
+        for (; c < dh; ++c) {
+            const float b = to_f32(cr[c]);
+#pragma unroll
+            for (int u = 0; u < TG; ++u) acc[u] = fmaf(to_f32(xr[(size_t)min(u, n - 1) * dk + c]), b, acc[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < TG; ++u)
+            if (u < n) scores[((tg + u) * NH + half - HB) * SP + j] = j < s ? acc[u] : -INFINITY;
+    }
+}
+
 // Phase A: sub-key scores of tokens t0 .. t0 + nt - 1 (nt <= AT) of one
 // stream (xs: its x, token stride dk; cbh: its head's codebook [2][s][dk/2],
 // unused in direct mode) into score rows 0 .. nt-1: row [NH][SP] for halves
 // HB .. HB + NH - 1 (both by default), half h's sub-key j at (h - HB) SP + j,
-// j in [s, SP) -inf.  Rows past nt are not written.
-template <typename XT, int MODE, int E, int HB = 0, int NH = 2>
+// j in [s, SP) -inf.  Rows past nt are not written.  TG: fma_scores' tokens per thread.
+template <typename XT, int MODE, int E, int HB = 0, int NH = 2, int TG = 8>
 __device__ __forceinline__ void tile_scores(const XT* __restrict__ xs, const XT* __restrict__ cbh, int t0, int nt,
                                             int dk, int s, float* scores) {
     constexpr int SP = E * SDM_WAVE;
@@ -775,43 +820,7 @@ __device__ __forceinline__ void tile_scores(const XT* __restrict__ xs, const XT*
             scores[i] = j >= s ? -INFINITY : to_f32(xs[(size_t)t * dk + half * s + j]);
         }
     } else if constexpr (MODE == 1) {
-        // Plain FMAs, each score one chain over its d_k / 2 terms in order.  A thread
-        // takes one sub-key for TG tokens, so the sub-key rows (a line per lane and
-        // load) are read once per TG tokens; the tokens' values are the same for the
-        // whole wave.  One sub-key and token per thread read a row per score: 206 us
-        // a side for 11,655 tokens at sqrt(N) = 100, d_k = 72, 51 now; 6.4 against 0.25 ms
-        // for 16,384 tokens at sqrt(N) = 512, d_k = 200.
-        constexpr int TG = 8;
-        const int dh = dk / 2;
-        for (int i = tid; i < (nt + TG - 1) / TG * NH * SP; i += blockDim.x) {
-            const int rest = __builtin_amdgcn_readfirstlane(i / SP), j = i - rest * SP;
-            const int half = HB + rest % NH, tg = rest / NH * TG, n = min(TG, nt - tg);
-            const XT* xr = xs + (size_t)(t0 + tg) * dk + half * dh;
-            const XT* cr = cbh + ((size_t)half * s + min(j, s - 1)) * dh;
-            float acc[TG];
-#pragma unroll
-            for (int u = 0; u < TG; ++u) acc[u] = 0.f;
-            int c = 0;
-            for (; c + 4 <= dh; c += 4) {
-                const v4f b = ld4_any(cr + c);
-#pragma unroll
-                for (int u = 0; u < TG; ++u) {
-                    const v4f a = ld4_any(xr + (size_t)min(u, n - 1) * dk + c);
-                    acc[u] = fmaf(a.x, b.x, acc[u]);
-                    acc[u] = fmaf(a.y, b.y, acc[u]);
-                    acc[u] = fmaf(a.z, b.z, acc[u]);
-                    acc[u] = fmaf(a.w, b.w, acc[u]);
-                }
-            }
-            for (; c < dh; ++c) {
-                const float b = to_f32(cr[c]);
-#pragma unroll
-                for (int u = 0; u < TG; ++u) acc[u] = fmaf(to_f32(xr[(size_t)min(u, n - 1) * dk + c]), b, acc[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < TG; ++u)
-                if (u < n) scores[((tg + u) * NH + half - HB) * SP + j] = j < s ? acc[u] : -INFINITY;
-        }
+        fma_scores<XT, E, HB, NH, TG>(xs, cbh, t0, nt, dk, s, scores);
     } else {
         // MFMA 16x16x32: A[i][kk] = x[t0+i][half*dh + kk], B[kk][j] = cb[half][j0+j][kk].
         // Lane l supplies row/col (l % 16) and k-slice 8*(l/16) .. +7 of each 32-deep step;
@@ -1556,8 +1565,8 @@ __global__ __launch_bounds__(AWAVES * SDM_WAVE) void decode_kernel(
             }
         }
         if (!joint) {
-            tile_scores<XT, MODE, E>(q + (size_t)stream * dk, MODE == 0 ? cb_q : cb_q + hc, 0, 1, dk, s, scores);
-            tile_scores<XT, MODE, E>(kx + (size_t)stream * dk, MODE == 0 ? cb_k : cb_k + hc, 0, 1, dk, s,
+            tile_scores<XT, MODE, E, 0, 2, 1>(q + (size_t)stream * dk, MODE == 0 ? cb_q : cb_q + hc, 0, 1, dk, s, scores);
+            tile_scores<XT, MODE, E, 0, 2, 1>(kx + (size_t)stream * dk, MODE == 0 ? cb_k : cb_k + hc, 0, 1, dk, s,
                                      scores + 2 * SP);
         }
         if (threadIdx.x < 2) fail[threadIdx.x] = 0;

@@ -29,3 +29,23 @@ def test_fma_scores(T, s, dh, k, dtype):
     kth = full.topk(k, dim=-1).values[..., -1]
     assert (score.double().min(-1).values - kth).abs().max() <= tol
     assert (val.double() - torch.softmax(score.double(), -1)).abs().max() <= 1e-6
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("s,dh,k", [(9, 1, 3), (64, 5, 33), (130, 18, 16), (300, 37, 20), (600, 100, 70), (1024, 3, 128)])
+def test_one_token_scores_as_many(s, dh, k, dtype):
+    """The decode step scores its single token by threads of one token, the tiles by
+    threads of eight: the same chains, so the same bits, also as in a tile of nine."""
+    g = torch.Generator(device=DEV).manual_seed(s + dh)
+    B, H, d_v = 2, 2, 8
+    x = torch.randn((B, H, 9, 2 * dh), generator=g, device=DEV).to(dtype)
+    cb = torch.randn((H, 2, s, dh), generator=g, device=DEV).to(dtype)
+    many = sdm.address(x, cb, s * s, k, want_score=True)
+    one = x[:, :, :1].contiguous()
+    for a, b in zip(sdm.address(one, cb, s * s, k, want_score=True), many):
+        assert torch.equal(a, b[:, :, :1])
+    z = torch.ones((B, H, 1), device=DEV).to(dtype)
+    o = sdm.forward(one, one, cb, cb, torch.zeros((B, H, 1, d_v), device=DEV).to(dtype), z, z,
+                    torch.zeros((B, H, s * s, d_v), device=DEV), s * s, k)
+    for name, b in (("r_idx", many[0]), ("r_val", many[1]), ("w_idx", many[0]), ("w_val", many[1])):
+        assert torch.equal(o[name], b[:, :, :1])
