@@ -357,7 +357,8 @@ hipError_t launch_bround_k(const ScanBwdArgs& a, const BRoundPlan& p, float* par
 // with (W + R)^2 / N.  Its time over this kernel's by that (d_v = 128; limits in
 // brackets):
 //   16 streams   top-16: 8 1.15, 1 1.50; top-24: 8 0.81, 1.4 0.96, 1 1.05 [1]
-//                top-48: 2 0.76, 0.7 0.99, 0.5 1.15 [1/2]
+//                top-48: 2 0.76, 0.7 1.08, 0.5 1.17; write 48, read 24: 0.6 0.94, 0.5 1.00
+//                [3/5] (4 streams 0.97 and 0.88 at 0.6, 60 streams 1.77 and 1.16)
 //   128 streams  top-12: 2 0.72, 0.5 1.10; top-16: 8 0.72, 2 1.00, 1 1.12 [1]
 //                top-24: 8 0.75, 1 1.04; top-40: 1 0.84, 0.7 1.03; top-48: 2 0.92, 1 1.11 [3/4]
 //   512 streams  top-24: 8 0.75, 1 1.03; top-40: 2 0.77, 0.7 1.01, 0.5 1.09; top-48: 1 1.08
@@ -377,7 +378,7 @@ bool sdm_bwd_round(const ScanBwdArgs& a) {
     if (m <= RG * 2) return wgs <= cus || a.N >= links;
     const int ragged = a.dv % CW && wgs > cus && (a.dv > 2 * CW || wgs < 4 * cus) ? 2 : 1;
     if (m <= RG * 4) return ragged * a.N >= links;
-    return wgs <= cus ? a.N >= 2 * links : 3 * ragged * a.N >= 4 * links;
+    return 3 * ragged * a.N >= (wgs <= cus ? 5 : 4) * links;
 }
 int sdm_bwd_round_parts(const ScanBwdArgs& a) { return bround_groups(a); }
 

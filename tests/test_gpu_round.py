@@ -227,7 +227,7 @@ def test_round_backward(name, dtype):
     (520, 341, 16, 0, 1, 0), (520, 342, 16, 1, 1, 0), (520, 1024, 16, 1, 1, 1),
     (4, 863, 24, 0, 0, 0), (4, 864, 24, 1, 1, 0), (4, 2304, 24, 1, 1, 1),
     (260, 921, 24, 0, 0, 0), (260, 2303, 24, 0, 1, 0), (260, 2304, 24, 1, 1, 1),
-    (4, 7679, 48, 0, 0, 0), (4, 7680, 48, 1, 1, 0), (4, 18432, 48, 1, 1, 1),
+    (4, 7679, 48, 0, 0, 0), (4, 7680, 48, 1, 1, 0), (4, 15359, 48, 1, 1, 0), (4, 15360, 48, 1, 1, 1),
     (260, 9215, 48, 0, 1, 0), (260, 9216, 48, 1, 1, 0), (260, 12288, 48, 1, 1, 1),
     (4, 3071, 32, 0, 0, 0), (4, 3072, 32, 1, 1, 1),                              # the line kernel's lists
     (4, 12287, 64, 0, 0, 0), (4, 12288, 64, 1, 1, 0), (4, 16384, 64, 1, 1, 1)]])
