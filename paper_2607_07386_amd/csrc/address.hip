@@ -2008,11 +2008,13 @@ hipError_t launch_decode_m(const void* q, const void* k, const void* cb_q, const
     const XT* kp = static_cast<const XT*>(k);
     const XT* cq = static_cast<const XT*>(cb_q);
     const XT* ck = static_cast<const XT*>(cb_k);
-    // Workgroups per stream: with fewer streams than two per compute unit and rows
-    // of several 128-column chunks the chunks go to workgroups of their own, each
-    // repeating the selection (the paper's 1.4B layer, 32 streams of d_v = 960: 54 us a layer call, 28 split).
+    // Workgroups per stream: rows of several 128-column chunks go to workgroups of their
+    // own, each repeating the selection, as long as each has a compute unit to itself:
+    // two do not run side by side (one chunk or two, us a step: 128 streams of d_v = 256
+    // top-32 18.7 / 16.4, 160: 18.8 / 30.2, 256: 19.4 / 30.7; the paper's 1.4B layer, 32
+    // streams of d_v = 960, a layer call: 54 in one, 28 in eight).
     const int chunks = (dv + DEC_COLS - 1) / DEC_COLS;
-    const unsigned split = std::max(1, std::min(chunks, sdm_device_simds() / 2 / (B * H)));
+    const unsigned split = std::max(1, std::min(chunks, sdm_device_simds() / 4 / (B * H)));
 #define SDM_DEC_CASE(EE, KM)                                                                              \
     {                                                                                                     \
         const size_t sm = decode_lds_bytes(EE, KM, topk);                                                  \
