@@ -477,7 +477,10 @@ bool sdm_round_scan(const ScanFwdArgs& a, int* per_log2, int* depth, int* lds) {
 //     32: 16,384 1484 / 1557; 64: 4096 2043 / 2224, 8192 2304 / 1912; 128: 4096 4065 / 3184.
 //     From 49 write rows on the chunk form holds fewer workgroups: top-56, 16 streams 8192
 //     1978 / 2119, 16,384 2011 / 1782; 64: 4096 2929 / 2590.  Narrow, write 8, read 64: 8
-//     streams 32,768 886 / 1000, 65,536 1005 / 942; 16: 16,384 1041 / 1113, 32,768 1190 / 1017.
+//     streams 32,768 886 / 1000, 65,536 1005 / 942; 16: 16,384 1041 / 1113, 32,768 1190 / 1017;
+//     1: 262,144 789 / 857 (write 32: 65,536 1120 / 1120, 262,144 1096 / 936): its narrow
+//     workgroups' time goes with the write rows.  Product keys of clustered tokens, whose
+//     slots recur: 8 streams of 32 columns, 4123 tokens, write 16, read 34, 65,536 1532 / 2208.
 //   Lists of exactly 64 rows (whole lines, no bounds checks): 16 streams 8192 2194 / 1825.
 bool sdm_round_beats_chunk(const ScanFwdArgs& a, bool narrow) {
     RoundPlan p;
@@ -489,7 +492,7 @@ bool sdm_round_beats_chunk(const ScanFwdArgs& a, bool narrow) {
     if (line_lists(a) && m == 64) return a.N >= pairs;
     if (a.W <= 32 && a.N < 10 * pairs) return false;
     if (m <= 32) return !narrow || a.N >= 20 * rows * rows;
-    if (narrow) return a.N >= 32768;
+    if (narrow) return a.N >= std::max<int64_t>(32768, (1 << 25) / (a.W * wgs));
     if (a.W > 48) return a.N >= std::max<int64_t>(4096, std::min<int64_t>(16384, (1 << 20) / wgs));
     return a.N >= std::max<int64_t>(4096, std::min<int64_t>(65536, (1 << 21) / wgs));
 }

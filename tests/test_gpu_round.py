@@ -158,7 +158,8 @@ def test_chunked_call_in_rounds(T):
     (65, 20480, 32, 32, 128, 0),                                                        # the line kernel's from here on
     (8, 65535, 40, 40, 128, 0), (8, 65536, 40, 40, 128, 1), (32, 16383, 48, 24, 128, 0), (32, 16384, 48, 24, 128, 1),
     (16, 16383, 56, 56, 128, 0), (16, 16384, 56, 56, 128, 1), (512, 4095, 40, 40, 32, 0), (512, 4096, 40, 40, 32, 1),
-    (8, 32767, 8, 64, 128, 0), (8, 32768, 8, 64, 128, 1), (4, 8191, 64, 64, 128, 0), (4, 8192, 64, 64, 128, 1)])
+    (32, 131071, 8, 64, 32, 0), (32, 131072, 8, 64, 32, 1), (32, 32767, 32, 64, 32, 0),
+    (32, 32768, 32, 64, 32, 1), (4, 8191, 64, 64, 128, 0), (4, 8192, 64, 64, 128, 1)])
 def test_which_chunked_calls_go_in_rounds(S, N, W, R, dv, rounds):
     """The chunk form keeps the tables on which tokens of a round share slots."""
     T = 64
