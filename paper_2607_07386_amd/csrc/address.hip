@@ -2009,10 +2009,11 @@ hipError_t launch_decode_m(const void* q, const void* k, const void* cb_q, const
     const XT* cq = static_cast<const XT*>(cb_q);
     const XT* ck = static_cast<const XT*>(cb_k);
     // Workgroups per stream: rows of several 128-column chunks go to workgroups of their
-    // own, each repeating the selection, as long as each has a compute unit to itself:
-    // two do not run side by side (one chunk or two, us a step: 128 streams of d_v = 256
-    // top-32 18.7 / 16.4, 160: 18.8 / 30.2, 256: 19.4 / 30.7; the paper's 1.4B layer, 32
-    // streams of d_v = 960, a layer call: 54 in one, 28 in eight).
+    // own, each repeating the selection, as long as each has a compute unit to itself: two
+    // do not run side by side, a wave holds all registers of a SIMD.  One workgroup a
+    // stream or two, us a step of top-32: 128 streams of d_v = 256 18.7 / 16.4, 160: 18.8 /
+    // 30.2, 256: 19.4 / 30.7; the paper's 1.4B layer, 32 streams of d_v = 960, a layer call:
+    // 54 in one, 28 in eight.
     const int chunks = (dv + DEC_COLS - 1) / DEC_COLS;
     const unsigned split = std::max(1, std::min(chunks, sdm_device_simds() / 4 / (B * H)));
 #define SDM_DEC_CASE(EE, KM)                                                                              \

@@ -28,10 +28,12 @@ constexpr int THREADS = 256;
 
 // Tokens per workgroup, a multiple of the round `per`.  A window of a few tokens
 // (reach) costs small workgroups little, and the records of those scans are built
-// beside a scan that fills the device: 8 tokens (6 KB of LDS at 32 rows) there take
-// the least from it (1.4B-shaped forward with 64, 32, 16, 8 tokens: 6.13, 6.08,
-// 6.02, 5.94 ms; training step 11.81, 11.74, 11.70, 11.57).  Deep windows, whose
-// lists every workgroup enters again, take 32, or 16 with long lists.
+// beside a scan that fills the device: 8 tokens (6 KB of LDS at 32 rows a side) there
+// take the least from it (1.4B-shaped forward with 64, 32, 16, 8 tokens: 6.13, 6.08,
+// 6.02, 5.94 ms; training step 11.81, 11.74, 11.70, 11.57).  At 64 rows the backward's 8
+// tokens take 12.5 KB, which the 64-row line kernel (154 KB) does not leave: those
+// records wait for its workgroups to end, whatever the count above two tokens.  Deep
+// windows, whose lists every workgroup enters again, take 32, or 16 with long lists.
 int prep_tokens(int nrow, int reach, int per) {
     return std::max(per, reach <= 8 ? 8 : nrow <= 96 ? 32 : 16);
 }

@@ -36,7 +36,7 @@
 // from the same XCD: the lines are then in its L2.  16 streams of 2048 tokens
 // (top-32, d_v = 128, N = 65536): 1112 us by the line kernel, 762 here, 551 with
 // two helpers per workgroup; 16 x 65,536 tokens (N = 262,144): 34.4, 24.4 and
-// 17.6 ms; two heads of d_v = 1920, top-64 (4096 tokens): 3.60, 3.23, 2.74 ms.
+// 16.0 ms; two heads of d_v = 1920, top-64 (4096 tokens): 3.60, 3.23, 2.74 ms.
 #include <algorithm>
 
 #include "sdm_common.h"
@@ -388,8 +388,8 @@ bool line_lists(const ScanFwdArgs& a) { return a.W == a.R && (a.W == 32 || a.W =
 //    streams, against the line kernel: N = 2048 155 / 170 us, 2925 153 / 153, 4096 152 /
 //    144; top-64: 8192 223 / 253, 11,702 220 / 234, 16,384 219 / 210).
 // Other lists would take the per-wave kernel, which moves 32-byte pieces of rows: it
-// loses on large tables (16 streams of 2048 tokens top-16 1705 / 410 us, 128 streams
-// top-8 1972 / 1176) and at up to 16 rows nearly everywhere.  On dense tables it wins
+// loses on large tables (2048 tokens, N = 65536, 16 streams top-16 1691 / 298 us, 128
+// streams top-8 1720 / 794) and at up to 16 rows nearly everywhere.  On dense tables it wins
 // with longer lists, and earlier where two workgroups share a compute unit; the undo
 // log's stores cost it more.  Its time over this kernel's (d_v = 128, by W (W + R) / N;
 // limits in brackets, without / with the log):
