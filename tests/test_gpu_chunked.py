@@ -19,7 +19,7 @@ from tests.gpu_util import DEV, init_memory, rel_err, to_dev
 from paper_2607_07386_amd import sdm
 
 pytestmark = pytest.mark.gpu
-# The spec bar for fp32 is 1e-4; held here to the 1e-5 regression bound
+# The parity bar for fp32 is 1e-4; held here to the 1e-5 regression bound
 # (measured errors are about 1e-7).
 TOL = 1e-5
 
